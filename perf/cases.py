@@ -34,7 +34,8 @@ def listed():
         # Small ragged stages, sizes off every tile edge.
         dict(solve, name="plan_ragged", task="plan", B=37, L_lo=2, L_hi=19, S=21, E=4999, window=7),
         # The batched workload (4): 64 stages of 6 to 24 layers, the plans of a window of budgets below E.
-        dict(solve, name="plan_batch_44", task="plan", data="structured", B=64, L_lo=6, L_hi=24, S=44, E=32768, window=256),
+        dict(solve, name="plan_batch_44", task="plan", data="structured", B=64, L_lo=6, L_hi=24, S=44, E=32768,
+             window=256),
         # The same size without argmin records and with Algorithm 3's overall-memory check.
         dict(solve, name="budget_batch_44", task="budget", data="structured", B=64, L_lo=6, L_hi=24, S=44, E=32768,
              values_only=True),
@@ -54,7 +55,7 @@ def listed():
     ]
 
 
-MODEL_SETS = {22: (8, True), 46: (64, True), 68: (8, False), 186: (64, False)}   # strategies: (devices, Takeaway #3)
+MODEL_SETS = {22: (8, True), 46: (64, True), 78: (16, False), 186: (64, False)}   # strategies: (devices, Takeaway #3)
 MOST_UPDATES = 6.0e10
 MOST_CELLS = 1.0e9
 
@@ -67,16 +68,18 @@ def draw(rng):
         if rng.random() < 0.2:
             data = rng.choice(["structured", "model"])
             c = dict(task="partition", data=data, pairs=4 * rng.randint(1, 8), Lm=rng.randint(16, 48),
-                     S=rng.choice([22, 44]) if data == "structured" else 22, E=log(1000, 32768), overall=rng.random() < 0.5)
+                     S=rng.choice([22, 44]) if data == "structured" else 22, overall=rng.random() < 0.5,
+                     E=log(16384 if data == "structured" else 4096, 32768))
             if c["pairs"] * 8.0 * c["Lm"] * c["E"] * c["S"] ** 2 <= 10 * MOST_UPDATES:
                 return c
             continue
         data = rng.choice(["structured", "uniform", "uniform", "model"])
         task = rng.choice(["plan", "curve", "budget"] + (["model"] if data == "model" else ["plan"]))
-        S = rng.choice([22, 44]) if data == "structured" else rng.choice(list(MODEL_SETS)) if data == "model" else log(3, 200)
-        lo = log(2, 48)
+        S = log(3, 200) if data == "uniform" else rng.choice([22, 44] if data == "structured" else list(MODEL_SETS))
+        lo = log(2, 24 if data == "structured" else 48)
+        floor = {"uniform": 256, "structured": 320 * (lo + 16), "model": 4096}[data]   # budgets that some plan fits
         c = dict(task=task, data=data, B=2 * log(1, 8) if data == "model" else log(1, 64), L_lo=lo,
-                 L_hi=lo if data == "model" else lo + rng.randint(0, 16), S=S, E=log(256, 65536),
+                 L_hi=lo if data == "model" else lo + rng.randint(0, 16), S=S, E=log(floor, 65536),
                  values_only=task == "budget" or rng.random() < 0.2, host=task != "model" and rng.random() < 0.3,
                  window=rng.choice([1, 1, 64, 256]))
         c["window"] = min(c["window"], c["E"] + 1)
@@ -186,8 +189,8 @@ def run(state):
     if case["task"] == "partition":
         a, over = state["a"], case["overall"]
         res, state["ctx"] = g.gbmw_partition_search(
-            a["P"], state["Lm"], state["m"], a["c"], a["cns"], a["R"], a["M"], a["p0"], a["p_t"], case["S"], case["E"],
-            max_iter=32, ctx=state["ctx"], batch_size=a["batch"], batch_group=a["group"],
+            a["P"], state["Lm"], state["m"], a["c"], a["cns"], a["R"], a["M"], a["p0"], a["p_t"], case["S"],
+            case["E"], max_iter=32, ctx=state["ctx"], batch_size=a["batch"], batch_group=a["group"],
             O_b=a["O_b"] if over else None, O_ms=a["O_ms"] if over else None)
         return {k: v for k, v in res.items() if k != "device_ms"}
     if case["task"] == "model":
@@ -195,7 +198,8 @@ def run(state):
     else:
         c, M, R = state["c"], state["M"], state["R"]
     flags = g.GBMW_FLAG_LAZY_ARGMIN if case["values_only"] else 0
-    state["ctx"] = ctx = g.gbmw_dp_solve_batched(state["L"], c, M, R, case["S"], case["E"], flags=flags, ctx=state["ctx"])
+    ctx = g.gbmw_dp_solve_batched(state["L"], c, M, R, case["S"], case["E"], flags=flags, ctx=state["ctx"])
+    state["ctx"] = ctx
     out = {}
     if case["task"] == "budget":
         out["budget"] = g.gbmw_select_forward_budget(ctx, *state["O"])
