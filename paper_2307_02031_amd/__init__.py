@@ -4,7 +4,7 @@ strategy search (Section 4.1.2, Eq. 3 and Appendix A of the paper).
 The functions here have the names of the C entry points in include/gbmw.h and
 only marshal arguments: every step of the search runs in the library's HIP
 kernels.  There is no CPU fallback -- if the library has not been built
-(``python -m paper_2307_02031_amd.build``) importing this package raises.
+(``python paper_2307_02031_amd/build.py``) importing this package raises.
 
 PyTorch is used for device memory and streams only: device-resident inputs are
 torch CUDA tensors whose ``data_ptr()`` is handed to the library, and work is
@@ -89,7 +89,7 @@ class GbmwError(RuntimeError):
 
 
 if not os.path.exists(LIB_PATH):
-    raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2307_02031_amd.build` "
+    raise ImportError(f"{LIB_PATH} is missing: build it with `python paper_2307_02031_amd/build.py` "
                       "(there is no CPU fallback)")
 _lib = ct.CDLL(LIB_PATH)
 _lib.gbmw_dp_solve_batched.argtypes = [ct.POINTER(gbmw_problem), ct.c_uint32, ct.POINTER(ct.c_void_p)]
