@@ -70,21 +70,19 @@ enum {
                                   arithmetic and tie rule, so every result is identical.
                                   The fill then costs one add and half a three-input min
                                   per candidate and nothing else                         */,
-  GBMW_FLAG_DENSE_ARITHMETIC = 32u /* every lane computes its own cell.  Default: a wave
-                                  whose 64 consecutive budgets all read the same column of
-                                  the previous layer's table (the tables are step functions
-                                  of the budget, so most waves do) computes that column's
-                                  cells once, one output strategy per lane.  Every layer
-                                  leaves one word per strategy and 64 budgets (1/64 of the
-                                  fp32 table bytes of device memory more) that holds such a
-                                  group's value: the next layer recognises its runs from
-                                  those words without reading the table, and the group's
-                                  cells are not written inside the library's own tables
-                                  (what gbmw_export_tables and every other call return is
-                                  unaffected).  Identical results either way; the flag
+  GBMW_FLAG_DENSE_ARITHMETIC = 32u /* every lane computes its own cell from every candidate.
+                                  Default, except for small problems: the tables are step
+                                  functions of the budget, and every layer leaves, per
+                                  strategy and 64 budgets, the group's first and last value
+                                  (1/32 of the fp32 table bytes of device memory more).  From
+                                  these the next layer knows which predecessors can still be
+                                  minimal in a group and which groups are constant; it
+                                  computes and writes only what they leave open
+                                  (the calls that hand tables out put them back together).
+                                  Identical results either way; this flag
                                   exists to time the dense arithmetic                     */,
-  GBMW_FLAG_COUNT_WORK = 64u   /* measurement: the min-plus launches also count the waves
-                                  that took the shortcut above, for gbmw_last_solve_work
+  GBMW_FLAG_COUNT_WORK = 64u   /* measurement: the min-plus launches also count the groups
+                                  that read one column, for gbmw_last_solve_work
                                   (implies GBMW_FLAG_ONE_STREAM).  The counts depend on the
                                   inputs alone; the counting costs registers, so time the
                                   kernels in a solve without this flag                    */,
@@ -497,19 +495,20 @@ gbmw_status gbmw_last_solve_ms(gbmw_ctx* ctx, float* total_ms, float* minplus_ms
                                int32_t* minplus_launches);
 
 /*
- * What the min-plus launches of the last solve really computed, for roofline
- * accounting (all zero unless the solve was given GBMW_FLAG_COUNT_WORK).  launch
- * selects one min-plus launch of the solve, in the order they were enqueued
+ * How the groups of 64 budgets of the last solve's min-plus launches divide into
+ * runs and others (all zero unless the solve was given GBMW_FLAG_COUNT_WORK).
+ * launch selects one min-plus launch of the solve, in the order they were enqueued
  * (0 is the launch of layer 1, whose input is layer 0's closed form and is not
- * read from memory), or -1 for the sum over all of them.  With the run shortcut
- * of Eq. 3's fill (see GBMW_FLAG_DENSE_ARITHMETIC) a group of budgets that reads
- * one and the same column of the previous table is computed once:
- *   work[0]  workgroups (256 budgets) computed once:      S * S candidate updates each
- *   work[1]  waves (64 budgets) computed once, recognised
- *            from the summaries:                          S * S updates each
- *   work[2]  the same, recognised from the loaded table:  S * S updates each
- *   work[3]  (wave, output strategy) rows computed cell
- *            by cell:                                     64 * S updates each
+ * read from memory), or -1 for the sum over all of them.  A run is a group whose
+ * budgets read one and the same column of the previous table:
+ *   work[0]  units of 256 budgets that are one run
+ *   work[1]  other groups of 64 budgets that are a run
+ *   work[2]  0
+ *   work[3]  (group, output strategy) rows of the groups that are not a run.  With
+ *            GBMW_FLAG_DENSE_ARITHMETIC (and where the dense kernels are taken by
+ *            themselves) every row of the tables: 64 * S candidate updates each.  By
+ *            default only the candidates that can still be minimal are computed, so
+ *            64 * S is an upper bound there
  * Waits for the solve.
  */
 gbmw_status gbmw_last_solve_work(gbmw_ctx* ctx, int32_t launch, uint64_t work[4]);

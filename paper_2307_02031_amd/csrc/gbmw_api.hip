@@ -96,7 +96,7 @@ void free_ctx(gbmw_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   for (DevBuf* b : {&c->d_L, &c->d_off, &c->d_perm, &c->d_c, &c->d_M, &c->d_R, &c->d_Rt, &c->d_C, &c->d_sum,
                     &c->d_A, &c->d_best, &c->d_best_s, &c->d_status, &c->d_q, &c->d_stage,
-                    &c->d_search, &c->d_gather, &c->d_counts, &c->d_sync, &c->d_asum})
+                    &c->d_search, &c->d_gather, &c->d_counts, &c->d_sync, &c->d_asum, &c->d_row})
     b->release();
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
@@ -298,6 +298,8 @@ gbmw_status gbmw_detail::solve_batched(const gbmw_problem* p, uint32_t flags, gb
   // a repeated solve of the same batch layout keeps the index arrays already on the device
   const bool same_layout = !fresh && c->index_on_device && c->L == L && c->off == off && c->perm == perm;
   c->L = L; c->off = off; c->perm = perm;
+  c->slots.resize(B);
+  for (int i = 0; i < B; ++i) c->slots[i] = make_int2(perm[i], off[perm[i]]);
   const int SP = c->SP, EP = c->EP;
   const bool lazy = (flags & GBMW_FLAG_LAZY_ARGMIN) != 0;
   // The single launch keeps every layer's table where that is cheap (a small problem by
@@ -310,14 +312,16 @@ gbmw_status gbmw_detail::solve_batched(const gbmw_problem* p, uint32_t flags, gb
 
   TRY(c->d_L.reserve(sizeof(int) * B));
   TRY(c->d_off.reserve(sizeof(int) * B));
-  TRY(c->d_perm.reserve(sizeof(int) * B));
+  TRY(c->d_perm.reserve(sizeof(int2) * B));
   TRY(c->d_status.reserve(sizeof(int)));
   const int RS = (SP + 2 + 3) / 4 * 4;
-  TRY(c->d_Rt.reserve(sizeof(float) * (size_t)sumL * S * RS));
   TRY(c->d_C.reserve(sizeof(float) * slab * (keep ? (size_t)sumL : (size_t)2 * B)));
-  // the run shortcut and its summaries exist for the register-blocked kernels (S <= 64)
-  const bool runs = (flags & GBMW_FLAG_DENSE_ARITHMETIC) == 0 && gbmw::layer0_in_registers(S) && !single;
-  if (runs) TRY(c->d_sum.reserve(sizeof(float) * ((size_t)S * (EP / 64)) * (keep ? (size_t)sumL : (size_t)2 * B)));
+  const bool runs = (flags & GBMW_FLAG_DENSE_ARITHMETIC) == 0 && !single &&
+                    gbmw::pruned_step_takes(S, E, (B + G - 1) / G, 400000000ll / G);
+  // the pruned step reads R as it comes, the dense kernels its transposed, padded form
+  TRY(c->d_Rt.reserve(sizeof(float) * (size_t)sumL * S * (runs ? S : RS)));
+  if (runs) TRY(c->d_row.reserve(sizeof(float4) * (size_t)sumL * S));
+  if (runs) TRY(c->d_sum.reserve(sizeof(float2) * ((size_t)S * (EP / 64)) * (keep ? (size_t)sumL : (size_t)2 * B)));
   if (!lazy) TRY(c->d_A.reserve(slab * (size_t)sumL));
   // with both, one record per group of 64 budgets where the group's 64 are equal (Tables::Asum)
   if (!lazy && runs) TRY(c->d_asum.reserve((size_t)S * (EP / 64) * (size_t)sumL));
@@ -363,7 +367,7 @@ gbmw_status gbmw_detail::solve_batched(const gbmw_problem* p, uint32_t flags, gb
     c->index_on_device = false;
     HIP_TRY_B(hipMemcpyAsync(c->d_L.p, c->L.data(), sizeof(int) * B, hipMemcpyHostToDevice, st));
     HIP_TRY_B(hipMemcpyAsync(c->d_off.p, c->off.data(), sizeof(int) * B, hipMemcpyHostToDevice, st));
-    HIP_TRY_B(hipMemcpyAsync(c->d_perm.p, c->perm.data(), sizeof(int) * B, hipMemcpyHostToDevice, st));
+    HIP_TRY_B(hipMemcpyAsync(c->d_perm.p, c->slots.data(), sizeof(int2) * B, hipMemcpyHostToDevice, st));
     c->index_on_device = true;
   }
 
@@ -371,14 +375,16 @@ gbmw_status gbmw_detail::solve_batched(const gbmw_problem* p, uint32_t flags, gb
   t.B = B; t.S = S; t.SP = SP; t.RS = RS; t.E = E; t.EP = EP; t.keep_all = keep ? 1 : 0;
   t.final_from = std::min(std::max(final_from, 0), E);
   t.runs = runs ? 1 : 0;
-  t.Tsum = runs ? (float*)c->d_sum.p : nullptr;
-  t.L = (const int*)c->d_L.p; t.off = (const int*)c->d_off.p; t.perm = (const int*)c->d_perm.p;
-  t.c = dc; t.M = dM; t.Rt = (const float*)c->d_Rt.p;
+  t.Tsum = runs ? (float2*)c->d_sum.p : nullptr;
+  t.L = (const int*)c->d_L.p; t.off = (const int*)c->d_off.p; t.perm = (const int2*)c->d_perm.p;
+  t.c = dc; t.M = dM;
+  t.Rt = runs ? nullptr : (const float*)c->d_Rt.p;
+  t.Rn = runs ? (const float*)c->d_Rt.p : nullptr;
+  t.Row = runs ? (const float4*)c->d_row.p : nullptr;
   t.Cbuf = (float*)c->d_C.p; t.A = lazy ? nullptr : (uint8_t*)c->d_A.p;
   t.Asum = (!lazy && runs) ? (uint8_t*)c->d_asum.p : nullptr;
   t.best = (float*)c->d_best.p; t.best_s = (uint8_t*)c->d_best_s.p;
   t.status = (int*)c->d_status.p;
-  t.prev_full = 0;
 
   c->timed_launches = 0;
   c->counted_launches = 0;
@@ -418,11 +424,11 @@ gbmw_status gbmw_detail::solve_batched(const gbmw_problem* p, uint32_t flags, gb
     return GBMW_OK;
   }
   HIP_TRY_B(hipEventRecord(c->ev0, st));
-  gbmw::launch_prepare(t, dR, src_c, src_M, sumL, p->ptr_space == GBMW_PTR_DEVICE, st);
+  gbmw::launch_prepare(t, dR, src_c, src_M, sumL, Lmax, p->ptr_space == GBMW_PTR_DEVICE, st);
   {
     // Layer 0 goes to memory only where something reads it from there.  Inside a
     // group the instances are ordered by L descending, so the short ones are a suffix.
-    const bool all = keep || !gbmw::layer0_in_registers(S);
+    const bool all = keep || !gbmw::layer0_in_registers(t);
     if (all) {
       gbmw::launch_init_layer0(t, 0, B, st);
     } else {
@@ -445,7 +451,7 @@ gbmw_status gbmw_detail::solve_batched(const gbmw_problem* p, uint32_t flags, gb
         t.counts = (unsigned long long*)c->d_counts.p + 4 * (size_t)c->counted_launches++;
         c->counted_waves.push_back((unsigned long long)na * (unsigned long long)((E + 64) / 64));
       }
-      gbmw::launch_minplus(t, l, gfirst[g], na, sg, l > 1 ? active_in_group(g, l - 1) : 0);
+      gbmw::launch_minplus(t, l, gfirst[g], na, sg);
       if (timed) {
         HIP_TRY_B(hipEventRecord(c->ev_layer[2 * c->timed_launches + 1], sg));
         ++c->timed_launches;
@@ -704,7 +710,7 @@ gbmw_status gbmw_export_tables(gbmw_ctx* c, int32_t inst, int32_t l0, int32_t l1
     if (C) {
       const size_t tab = c->t.keep_all ? (size_t)(row0 + l) : (size_t)(l & 1) * c->B + inst;   // as c_table / sum_table
       const float* src = (const float*)c->d_C.p + tab * slab;
-      const float* sum = c->t.Tsum ? c->t.Tsum + tab * (S * (c->EP >> 6)) : nullptr;
+      const float2* sum = c->t.Tsum ? c->t.Tsum + tab * (S * (c->EP >> 6)) : nullptr;
       gbmw::launch_export_c(c->t, src, sum, c->t.M + (size_t)(row0 + l) * S, (float*)c->d_stage.p, c->stream);
       HIP_TRY(hipGetLastError());
       HIP_TRY(hipMemcpyAsync(C + (size_t)(l - l0) * rows * S, c->d_stage.p, rows * S * sizeof(float),

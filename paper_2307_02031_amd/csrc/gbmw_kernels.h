@@ -24,30 +24,32 @@ struct Tables {
   int B, S, SP, RS, E, EP;
   int keep_all;        // 1: Call[row][S][EP] for every layer row; 0: rolling pair
   int final_from;      // the final reduce fills best / best_s for e >= final_from only
-  int prev_full;       // set per launch: the input tables have every cell written (see runs)
-  int runs;            // != 0: a wave whose 64 budgets all have the same input column (the tables are
-                       // step functions of the budget) computes that column once, one output
-                       // strategy per lane, and leaves its cells of the fp32 table unwritten: the
+  int runs;            // != 0: the layer step looks only at the columns that can still be minimal over
+                       // a group of 64 budgets and computes the group once where they are constant
+                       // (gbmw_pruned.h); cells whose group is constant are left unwritten: the
                        // summaries say what they hold (see Tsum and table_cell); 0: every lane
                        // computes and writes its own cell, and there are no summaries
   const int* L;        // [B]   device
   const int* off;      // [B]   device, first row of each instance
-  const int* perm;     // [B]   device, instances ordered by L descending
+  const int2* perm;    // [B]   device, (instance, its first row) ordered by L descending
   const float* c;      // [sumL][S]  owned by the context (a copy of the caller's)
   const int* M;        // [sumL][S]  owned by the context
-  const float* Rt;     // [sumL][S][RS]
+  const float* Rt;     // [sumL][S][RS]  when runs == 0
+  const float* Rn;     // [sumL][S][S]   when runs != 0: R as it comes, R[row][s'][s], kept by the context
+  const float4* Row;   // [sumL][S]      when runs != 0 (layers >= 1): smallest and largest entry of row s' of R,
+                       // then c[row][s'] and the bits of M[row][s']
   float* Cbuf;         // keep_all ? [sumL][S][EP] : [2][B][S][EP]
   uint8_t* A;          // [sumL][S][EP]; null: records are not kept (needs keep_all), the
                        // walkers recompute the one they need from the kept tables
-  float* Tsum;         // per table (indexed like Cbuf) [S][EP/64]: for every strategy and every group
-                       // of 64 budgets e' of the layer's min-plus product, the value T + c if it is the
-                       // same for all 64 (those inside the table), NaN otherwise; written by every
-                       // launch when runs != 0; null when runs == 0.  Where the word is a number the
-                       // table's cells of that group (at e = e' + M) may be unwritten; where it is
-                       // NaN they are written
+  float2* Tsum;        // per table (indexed like Cbuf) [S][EP/64]: for every strategy and every group
+                       // of 64 budgets e' of the layer's min-plus product, the value T + c at the
+                       // group's first and at its last budget (inside the table); written by every
+                       // launch when runs != 0; null when runs == 0.  T + c is non-increasing along
+                       // the budgets: where the two are equal the group is constant and the table's
+                       // cells of that group (at e = e' + M) are unwritten; where they differ the
+                       // cells are written
   uint8_t* Asum;       // [sumL][S][EP/64], beside A when runs != 0, else null: the record of a whole
-                       // group of 64 budgets e' where one record holds for all of them (the groups whose
-                       // summary word in Tsum is a number: equal input columns give equal minimisers),
+                       // group of 64 budgets e' where one record holds for all of them,
                        // kNoGroupRecord where the group's records are in A.  Every launch that writes
                        // records writes this byte for every group it covers, and the 64 bytes of A only
                        // for the groups it marks kNoGroupRecord
@@ -63,25 +65,26 @@ struct Tables {
 };
 
 #if defined(__HIPCC__)
-constexpr int kNaNBits = 0x7fc00000;
-__device__ __forceinline__ bool is_nan_bits(int b) { return (b & 0x7fffffff) > 0x7f800000; }
-
 // C(l, e, s) of the layer whose table starts at Ctab ([S][EP]), whose summaries start at Tsum_tab
 // ([S][EP/64], unused when runs == 0) and whose M row is Mrow: +inf below M(l, s) (a negative M, or
 // one beyond the budget axis, leaves no feasible budget), else the summary of the group that
-// e - M falls in if it is a number, else the table's cell.
+// e - M falls in if its two ends are equal, else the table's cell.
 __device__ __forceinline__ float table_cell(const Tables& t, const float* __restrict__ Ctab,
-                                            const float* __restrict__ Tsum_tab, const int* __restrict__ Mrow,
+                                            const float2* __restrict__ Tsum_tab, const int* __restrict__ Mrow,
                                             int s, int e) {
   if (t.runs == 0) return Ctab[(size_t)s * t.EP + e];
   const int m = Mrow[s];
   if (m < 0 || e < m) return INFINITY;
-  const float w = Tsum_tab[(size_t)s * (t.EP >> 6) + ((e - m) >> 6)];
-  return is_nan_bits(__float_as_int(w)) ? Ctab[(size_t)s * t.EP + e] : w;
+  const float2 w = Tsum_tab[(size_t)s * (t.EP >> 6) + ((e - m) >> 6)];
+  return __float_as_int(w.x) == __float_as_int(w.y) ? w.x : Ctab[(size_t)s * t.EP + e];
 }
 
-// Marks a group of 64 budgets whose records are in A (strategy indices with the run shortcut
-// stay below 64).
+// R(l, s', s) of table row `row`.
+__device__ __forceinline__ float r_entry(const Tables& t, int row, int sp, int s) {
+  return t.runs != 0 ? t.Rn[((size_t)row * t.S + sp) * t.S + s] : t.Rt[((size_t)row * t.S + s) * t.RS + sp];
+}
+
+// Marks a group of 64 budgets whose records are in A (no strategy index of the pruned step: S < 256).
 constexpr int kNoGroupRecord = 0xff;
 
 // The argmin record of table row `row`, strategy s, budget e' = e (t.A != null).  Both bytes are
@@ -100,13 +103,38 @@ __device__ __forceinline__ int record(const Tables& t, int row, int s, int e) {
 __device__ __forceinline__ int pred_strategy(const Tables& t, int row, int s, int e) {
   if (t.A) return record(t, row, s, e);
   const float* __restrict__ Cp = t.Cbuf + (size_t)(row - 1) * t.S * t.EP;
-  const float* __restrict__ Tp = t.Tsum ? t.Tsum + (size_t)(row - 1) * t.S * (t.EP >> 6) : nullptr;
+  const float2* __restrict__ Tp = t.Tsum ? t.Tsum + (size_t)(row - 1) * t.S * (t.EP >> 6) : nullptr;
   const int* __restrict__ Mp = t.M + (size_t)(row - 1) * t.S;
-  const float* __restrict__ Rr = t.Rt + ((size_t)row * t.S + s) * t.RS;
   float best = INFINITY;
   int a = 0;
-  for (int sp = 0; sp < t.S; ++sp) {
-    const float x = table_cell(t, Cp, Tp, Mp, sp, e) + Rr[sp];
+  int sp = 0;
+  if (t.runs != 0) {
+    // table_cell for eight candidates at a time, all loads of a kind in flight together: a word, a
+    // cell and an entry of R each, whether the cell is then used or not (one candidate after the
+    // other is three memory round trips per candidate)
+    for (; sp + 8 <= t.S; sp += 8) {
+      int m[8];
+      float2 w[8];
+      float cell[8], r[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m[i] = Mp[sp + i];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int at = m[i] < 0 || e < m[i] ? 0 : (e - m[i]) >> 6;
+        w[i] = Tp[(size_t)(sp + i) * (t.EP >> 6) + at];
+        cell[i] = Cp[(size_t)(sp + i) * t.EP + e];
+        r[i] = t.Rn[((size_t)row * t.S + sp + i) * t.S + s];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float v = m[i] < 0 || e < m[i] ? INFINITY : __float_as_int(w[i].x) == __float_as_int(w[i].y) ? w[i].x : cell[i];
+        const float x = v + r[i];
+        if (x < best) { best = x; a = sp + i; }
+      }
+    }
+  }
+  for (; sp < t.S; ++sp) {
+    const float x = table_cell(t, Cp, Tp, Mp, sp, e) + r_entry(t, row, sp, s);
     if (x < best) { best = x; a = sp; }
   }
   return a;
@@ -118,13 +146,12 @@ __device__ __forceinline__ int pred_strategy(const Tables& t, int row, int s, in
 __device__ __forceinline__ int pred_strategy_wave(const Tables& t, int row, int s, int e, int lane) {
   if (t.A) return record(t, row, s, e);
   const float* __restrict__ Cp = t.Cbuf + (size_t)(row - 1) * t.S * t.EP;
-  const float* __restrict__ Tp = t.Tsum ? t.Tsum + (size_t)(row - 1) * t.S * (t.EP >> 6) : nullptr;
+  const float2* __restrict__ Tp = t.Tsum ? t.Tsum + (size_t)(row - 1) * t.S * (t.EP >> 6) : nullptr;
   const int* __restrict__ Mp = t.M + (size_t)(row - 1) * t.S;
-  const float* __restrict__ Rr = t.Rt + ((size_t)row * t.S + s) * t.RS;
   float best = INFINITY;
   int a = 0x7fffffff;
   for (int sp = lane; sp < t.S; sp += 64) {
-    const float x = table_cell(t, Cp, Tp, Mp, sp, e) + Rr[sp];
+    const float x = table_cell(t, Cp, Tp, Mp, sp, e) + r_entry(t, row, sp, s);
     if (x < best) { best = x; a = sp; }
   }
   for (int d = 32; d >= 1; d >>= 1) {
@@ -139,7 +166,7 @@ __device__ __forceinline__ int pred_strategy_wave(const Tables& t, int row, int 
 // R -> Rt (transpose + pad), validation of device-resident inputs, and the copy of the
 // caller's c / M (src_c, src_M) into the context's own arrays t.c / t.M where they differ.
 void launch_prepare(const Tables& t, const float* R, const float* src_c, const int* src_M, int sumL,
-                    bool validate, hipStream_t st);
+                    int Lmax, bool validate, hipStream_t st);
 // Zeroes n measurement counters (a fill kernel, not a memset node).
 void launch_clear_counts(unsigned long long* counts, int n, hipStream_t st);
 // C(0, e, s) written to the table for instances perm[first .. first + count).  Needed
@@ -147,16 +174,14 @@ void launch_clear_counts(unsigned long long* counts, int n, hipStream_t st);
 // export), every instance when all layers are kept or S > 64.
 void launch_init_layer0(const Tables& t, int first, int count, hipStream_t st);
 // True when the layer-1 launch builds layer 0 in registers and does not read it.
-bool layer0_in_registers(int S);
+bool layer0_in_registers(const Tables& t);
+// True when a solve of n instances per launch takes the pruned layer step (Tables::runs);
+// most_dense_updates: candidate updates per layer from which it pays whatever the launch's size.
+bool pruned_step_takes(int S, int E, int n, long long most_dense_updates);
 // One layer l >= 1 for instances perm[first .. first + n_active):
 // min-plus product with argmin, fused with the shift by M(l,s), the + c(l,s)
 // and the +inf prefix.
-// n_prev: instances in the launch that produced this one's input tables (layer l - 1 of the same
-// instances and more); 0 if not known (tables kept from other launches); < 0: whatever produced
-// them wrote every cell (split launches: launch_is_split).
-void launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t st, int n_prev = 0);
-// Does a launch over n_active instances take the split shape (which writes every table cell)?
-bool launch_is_split(const Tables& t, int n_active);
+void launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t st);
 // best(e), best_s(e) for e = final_from .. E over the last layer of instances
 // perm[first .. first + count).
 void launch_final(const Tables& t, int first, int count, hipStream_t st);
@@ -176,7 +201,7 @@ void launch_pipeline_cost(const Tables& t, int n_stage, const int* st_inst, cons
                           float* cost, hipStream_t st);
 // [S][EP] -> [E+1][S] for rows [row0, row0+n) of C (fp32; base pointer given) or A (bytes).
 // C(l, ., .) of one layer as [E+1][S]; Ctab / Tsum_tab / Mrow as for table_cell.
-void launch_export_c(const Tables& t, const float* Ctab, const float* Tsum_tab, const int* Mrow, float* dst,
+void launch_export_c(const Tables& t, const float* Ctab, const float2* Tsum_tab, const int* Mrow, float* dst,
                      hipStream_t st);
 void launch_export_u8(const uint8_t* src, uint8_t* dst, int n, int S, int E, int EP, hipStream_t st);
 // The argmin records of one table row, [S][EP] bytes, recomputed from the kept tables.

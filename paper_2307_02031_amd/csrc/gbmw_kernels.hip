@@ -4,6 +4,7 @@
 // are not used: the work is fp32 VALU adds and mins with wave-uniform R
 // operands, streamed along the budget axis.
 #include "gbmw_kernels.h"
+#include "gbmw_pruned.h"
 
 #include <math.h>
 
@@ -19,25 +20,6 @@ __device__ __forceinline__ const GBMW_AS4 T* as_const(const T* p) {
 #pragma clang diagnostic ignored "-Wold-style-cast"
   return (const GBMW_AS4 T*)(p);
 #pragma clang diagnostic pop
-}
-
-// Summary of a table, laid out and indexed like the table itself: [S][EP / 64].
-__device__ __forceinline__ float* sum_table(const Tables& t, int inst, int row, int l) {
-  const size_t slab = (size_t)t.S * (t.EP >> 6);
-  return t.keep_all ? t.Tsum + (size_t)row * slab
-                    : t.Tsum + ((size_t)(l & 1) * t.B + inst) * slab;
-}
-
-
-// The group records of table row `row`: [S][EP / 64] bytes (null without them).
-__device__ __forceinline__ uint8_t* group_records(const Tables& t, int row) {
-  return t.Asum ? t.Asum + (size_t)row * t.S * (t.EP >> 6) : nullptr;
-}
-
-__device__ __forceinline__ float* c_table(const Tables& t, int inst, int row, int l) {
-  const size_t slab = (size_t)t.S * t.EP;
-  return t.keep_all ? t.Cbuf + (size_t)row * slab
-                    : t.Cbuf + ((size_t)(l & 1) * t.B + inst) * slab;
 }
 
 // ---------------------------------------------------------------------------
@@ -78,6 +60,38 @@ __global__ __launch_bounds__(256) void k_prepare(Tables t, const float* __restri
   if (validate && bad) atomicOr(t.status, bad);
 }
 
+// The same for the pruned layer step (t.runs != 0): R is kept as it comes, a row s' of a layer being
+// the S costs of leaving s' (what the step's lanes, one per output strategy, read), and every row
+// leaves its smallest and largest entry beside c and M (t.Row).  The l == 0 slab of R is ignored by contract and
+// may hold anything: it is neither read nor checked.  One wave per row, four rows in flight.
+__global__ __launch_bounds__(256) void k_prepare_runs(Tables t, const float* __restrict__ R, int validate,
+                                                      float* __restrict__ Rn, float4* __restrict__ Row,
+                                                      const float* __restrict__ src_c, const int* __restrict__ src_M) {
+  const int l = blockIdx.x, inst = blockIdx.y, S = t.S;
+  if (l >= t.L[inst]) return;
+  const size_t row = (size_t)t.off[inst] + l;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int bad = 0;
+  if (blockIdx.z == 0 && (int)threadIdx.x < S) {   // S < 256
+    const size_t i = row * S + threadIdx.x;
+    const float v = src_c[i];
+    const int m = src_M[i];
+    if (!(v >= 0.0f)) bad |= 1;
+    if (m < 0) bad |= 2;
+    if (src_c != t.c) {
+      const_cast<float*>(t.c)[i] = v;
+      const_cast<int*>(t.M)[i] = m;
+    }
+  }
+  if (l > 0) {
+    const int s0 = ((int)blockIdx.z * 4 + wave) * 4;
+    if (s0 < S && !row_limits<4>(R + row * S * S, S, s0, lane, src_c + row * S, src_M + row * S, Rn + row * S * S,
+                                   Row + row * S))
+      bad |= 4;
+  }
+  if (validate && bad) atomicOr(t.status, bad);
+}
+
 // R is validated per instance because the l == 0 slab is ignored by contract
 // and may hold anything.
 __global__ __launch_bounds__(256) void k_validate_R(Tables t, const float* __restrict__ R) {
@@ -105,9 +119,14 @@ void launch_clear_counts(unsigned long long* counts, int n, hipStream_t st) {
 }
 
 void launch_prepare(const Tables& t, const float* R, const float* src_c, const int* src_M, int sumL,
-                    bool validate, hipStream_t st) {
+                    int Lmax, bool validate, hipStream_t st) {
   // a fill kernel rather than a memset node, so that the sequence can be captured
   hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(1), 0, st, t.status);
+  if (t.runs != 0) {
+    hipLaunchKernelGGL(k_prepare_runs, dim3(Lmax, t.B, (t.S + 15) / 16), dim3(256), 0, st, t, R, validate ? 1 : 0,
+                       const_cast<float*>(t.Rn), const_cast<float4*>(t.Row), src_c, src_M);
+    return;
+  }
   const size_t n = (size_t)sumL * t.S * t.RS;
   int blocks = (int)((n + 255) / 256);
   if (blocks > 65536) blocks = 65536;
@@ -121,7 +140,7 @@ void launch_prepare(const Tables& t, const float* R, const float* src_c, const i
 // layer 0:  C(0, e, s) = e >= M(0, s) ? c(0, s) : +inf
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_init_layer0(Tables t, int first) {
-  const int inst = t.perm[first + blockIdx.z], s = blockIdx.y;
+  const int inst = t.perm[first + blockIdx.z].x, s = blockIdx.y;
   const int e = (blockIdx.x * 256 + threadIdx.x) * 4;     // EP is a multiple of 256: whole float4s
   if (e >= t.EP) return;
   const int row = t.off[inst];
@@ -134,8 +153,9 @@ __global__ __launch_bounds__(256) void k_init_layer0(Tables t, int first) {
   v.z = (m >= 0 && e + 2 >= m && e + 2 <= t.E) ? cs : INFINITY;
   v.w = (m >= 0 && e + 3 >= m && e + 3 <= t.E) ? cs : INFINITY;
   *reinterpret_cast<float4*>(C0 + (size_t)s * t.EP + e) = v;
-  // T + c of layer 0 is c(0, s) at every budget: one summary word per group of 64
-  if (t.runs != 0 && (e & 63) == 0 && e <= t.E) sum_table(t, inst, row, 0)[(size_t)s * (t.EP >> 6) + (e >> 6)] = cs;
+  // T + c of layer 0 is c(0, s) at every budget: the same summary for every group of 64
+  if (t.runs != 0 && (e & 63) == 0 && e <= t.E)
+    sum_table(t, inst, row, 0)[(size_t)s * (t.EP >> 6) + (e >> 6)] = make_float2(cs, cs);
 }
 
 void launch_init_layer0(const Tables& t, int first, int count, hipStream_t st) {
@@ -178,97 +198,15 @@ __device__ __forceinline__ float fmin3(float a, float b, float c) {
   return __builtin_fminf(__builtin_fminf(a, b), c);
 }
 
-// A wave whose 64 budgets all carry the same column C_{l-1}[e'][.] (a run of the step function
-// that the table is along the budget axis) has 64 identical cells per output strategy.  It is
-// computed once, with the lanes over the output strategies instead (colv: lane s' holds
-// column[s'], +inf beyond the last strategy): lane j forms
-// min_s' (column[s'] + R[s'][s_begin + j]) with the lowest minimising s' (strict compare in index
-// order) and adds c.  Same operands and operations per cell as the dense path, hence the same
-// bits.  The value goes into the layer's summary word of that group and strategy and nowhere
-// else: the 64 cells of the fp32 table stay unwritten, every reader takes the word where it is
-// a number (table_cell).  The argmin record, one for the 64 budgets as well, goes into the
-// group's byte of the row's group records (Tables::Asum) and the 64 bytes of A stay unwritten.
-template <int SP>
-__device__ __forceinline__ void uniform_min(const float colv, const float4* rt_lds, int srow, int& outv,
-                                            int& a) {
-  constexpr int RS = (SP + 2 + 3) / 4 * 4;
-  constexpr int RQ = RS / 4;
-  float best = INFINITY, cs = 0.0f;
-  a = 0;
-  int roff = srow * RQ;
-#pragma unroll
-  for (int q = 0; q < RQ; ++q) {
-    // one quad of the row in flight at a time: the read of quad q waits for the fold of quad
-    // q - 1, so that the row never occupies more than four registers (this path is bound by
-    // its stores, not by this latency)
-    asm volatile("" : "+v"(roff), "+v"(best));
-    const float4 v = rt_lds[roff + q];
-    const float rq[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      const int i = 4 * q + i4;
-      if (i < SP) {
-        const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(colv), i));
-        const float x = f + rq[i4];
-        if (x < best) { best = x; a = i; }
-      }
-    }
-    if (4 * q == SP) cs = rq[0];
-  }
-  outv = __float_as_int(best + cs);
-}
-
-template <int SP, bool ARG>
-__device__ __forceinline__ void uniform_tile(const float colv, const float4* rt_lds, int s_begin,
-                                             int s_end, int lane, int e0, int wbase, float* __restrict__ Cn,
-                                             uint8_t* __restrict__ Ag, float* __restrict__ sum_cur, int E,
-                                             int EP, unsigned long long* cnt) {
-  const int srow = (s_begin + lane < s_end) ? s_begin + lane : s_begin;   // idle lanes redo a valid row
-  int outv, a;
-  uniform_min<SP>(colv, rt_lds, srow, outv, a);
-  // the layer's own summary: every strategy's 64 cells are equal
-  if (s_begin + lane < s_end) sum_cur[(size_t)(s_begin + lane) * (EP >> 6) + (wbase >> 6)] = __int_as_float(outv);
-  // the summary word stands for the 64 cells, and one byte for their 64 records
-  if (ARG && s_begin + lane < s_end) Ag[(size_t)(s_begin + lane) * (EP >> 6) + (wbase >> 6)] = (uint8_t)a;
-  if (cnt && lane == 0) atomicAdd(cnt, 1ull);             // measurement only, when nothing else is live
-}
-
-// The same for a whole workgroup whose four waves (256 budgets from `base`) all carry that one
-// column: lane j writes the four summary words of strategy s_begin + j and, with records, the
-// four group records (one dword: EP is a multiple of 256, so a row of group records is whole
-// dwords and `base >> 6` a multiple of 4).
-template <int SP, bool ARG>
-__device__ __forceinline__ void wide_tile(const float colv, const float4* rt_lds, int s_begin, int s_end,
-                                          int lane, int base, float* __restrict__ Cn,
-                                          uint8_t* __restrict__ Ag, float* __restrict__ sum_cur, int E,
-                                          int EP, unsigned long long* cnt, int inside) {
-  const int srow = (s_begin + lane < s_end) ? s_begin + lane : s_begin;
-  int outv, a;
-  uniform_min<SP>(colv, rt_lds, srow, outv, a);
-  if (s_begin + lane < s_end) {
-    float* sp_ = sum_cur + (size_t)(s_begin + lane) * (EP >> 6) + (base >> 6);
-    const int last_group = E >> 6;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if ((base >> 6) + k <= last_group) sp_[k] = __int_as_float(outv);
-  }
-  if (ARG && s_begin + lane < s_end)
-    *reinterpret_cast<uint32_t*>(Ag + (size_t)(s_begin + lane) * (EP >> 6) + (base >> 6)) = (unsigned)a * 0x01010101u;
-  if (cnt && threadIdx.x == 0) {                          // measurement only: workgroups, and their waves
-    atomicAdd(cnt, 1ull);
-    atomicAdd(cnt + 3, (unsigned long long)inside);
-  }
-}
-
 // How a launch's workgroups map to (instance, tile): the divisors of that mapping come with
 // floor(2^32 / d) from the host, so that a workgroup finds its place with a multiply, a
 // subtract and one correction per division (the quotient estimate is never more than one
 // short) instead of the thirty-instruction sequence of a division by a run-time value: every
 // wave pays for them before it can ask for its first byte.
-constexpr int kDealChunk = 4;                            // consecutive tiles of one instance per XCD
 struct Deal {
   int n;                                                 // instances in the launch
-  unsigned inv_tiles, inv_rowlen, inv_cl, inv_n;         // of tiles, n * kDealChunk, tiles % kDealChunk, n
+  unsigned inv_tiles, inv_n;                             // of the tiles of an instance, and of n
+  int unit;                                              // pruned step: groups of 64 budgets per wave
 };
 
 __device__ __forceinline__ void divmod(unsigned p, unsigned d, unsigned inv, int& q, int& r) {
@@ -279,84 +217,33 @@ __device__ __forceinline__ void divmod(unsigned p, unsigned d, unsigned inv, int
 
 static unsigned inv_of(unsigned d) { return d <= 1 ? 0xffffffffu : (unsigned)((1ull << 32) / d); }
 
-static Deal make_deal(int tiles, int n) {
-  Deal d;
-  d.n = n;
-  d.inv_tiles = inv_of((unsigned)tiles);
-  d.inv_rowlen = inv_of((unsigned)(n * kDealChunk));
-  d.inv_cl = inv_of((unsigned)(tiles % kDealChunk));
-  d.inv_n = inv_of((unsigned)n);
-  return d;
+static Deal make_deal(int tiles, int n, int unit = 1) {
+  return Deal{n, inv_of((unsigned)tiles), inv_of((unsigned)n), unit};
 }
 
-// RUNS: waves whose budgets share one input column take uniform_tile (never in split mode:
-// those launches are bound by a wave's own latency, which the test would lengthen).
-// COUNT: the same kernel with one atomic per run-path wave or workgroup into t.counts, for
-// measurements.  The paths a wave takes depend on the inputs alone, so the counts of this
-// instantiation are those of the plain one, which is the one that is timed (the atomics cost a
-// few registers, and with them occupancy at some sizes).
+// RUNS: the pruned step (gbmw_pruned.h) instead of the dense arithmetic.
+// COUNT: the same with counts of the groups that read one column (t.counts), for measurements.
 template <int SP, int K, int NW, int CH, int MINW, bool FIRST, bool ARG, bool SPLIT, bool RUNS, bool COUNT = false>
 __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int tiles, int first, Deal deal) {
   constexpr bool split = SPLIT;
-  static_assert(!(SPLIT && RUNS), "no run shortcut in split mode");
+  static_assert(!(SPLIT && RUNS), "the pruned step has no split mode");
   static_assert(RUNS || !COUNT, "only the run paths are counted");
-  unsigned long long* const counts = COUNT ? t.counts : nullptr;
-  // With the run shortcut the waves that compute every cell are few and sit among waves that
-  // hardly use the VALU: nothing hides the latency of their reads of the R tile, so they keep
-  // PD quads of R in flight ahead of the fold, across the end of the row into the next one
-  // (a rotating software pipeline: the fold of a quad takes about 30 cycles, an LDS read
-  // about 130; the whole next row, tried first, costs 48 registers instead of 16 and with them
-  // a wave per SIMD).
-  constexpr bool PRE = RUNS && SP <= 56;                 // beyond, the table values leave no room for it
+  extern __shared__ float4 rt_lds[];                     // [S][RQ], or the pruned step's columns
+  if constexpr (RUNS) {
+    // all instances' low budgets first: the groups that are not constant lie there, and they take
+    // the longest
+    int place, slot;
+    divmod(blockIdx.x, (unsigned)deal.n, deal.inv_n, place, slot);
+    pruned_step<1, (COUNT ? 4 : kept(SP)), FIRST, ARG, COUNT>(t, l, t.perm[first + slot], place, tiles, deal.unit,
+                                                                 reinterpret_cast<float*>(rt_lds));
+  } else {
   constexpr int NC = (SP + CH - 1) / CH;                 // chunks (last may be short)
   constexpr int NP = NC / 2 + 1;                         // prefix minima / blocks
   constexpr int RS = (SP + 2 + 3) / 4 * 4;               // row: SP x R, c, M, padding
   constexpr int RQ = RS / 4;
-  constexpr int PD = 4;                                  // quads of R in flight ahead of the fold (PRE)
-  constexpr int RQP = (RQ + PD - 1) / PD * PD;           // the row's quads, padded to whole rounds of PD
-  extern __shared__ float4 rt_lds[];                     // [S][RQ]
-
-  // Workgroups go to the 8 XCDs (each with its own L2) round-robin by their index, and an XCD
-  // works through its share in index order.  With the run shortcut the (instance, tile) pairs
-  // are dealt out accordingly:
-  //  - in chunks of kChunk consecutive tiles of one instance per XCD, so that neighbouring
-  //    tiles, whose shifted stores share a cache line at their common border, mostly meet in
-  //    one L2;
-  //  - chunk row by chunk row across the instances (all chunks 0, then all chunks 1, ...): the
-  //    tiles that must be computed cell by cell lie at the low budgets of every instance and
-  //    take many times longer than the others, so they have to start early, all of them, and
-  //    leave the end of the launch to the quick ones;
-  //  - each chunk row starting one instance further on, so that the chunks of an instance go
-  //    round the XCDs instead of all landing on one: the instances differ in how many such
-  //    tiles they have, and an XCD cannot take work from another.
-  // With dense arithmetic every tile costs the same and the plain order is kept.
   int slot, tile;
-  if (RUNS) {
-    constexpr int kChunk = kDealChunk, kRound = 8 * kChunk;   // one round: a chunk for each XCD
-    const int b = blockIdx.x, nb = gridDim.x, n = deal.n;
-    int p = b;                                            // place in the dealt order (the ragged end keeps its own)
-    if (b < nb / kRound * kRound) {
-      const int w = b % kRound;                           // b = 8 * (round * kChunk + r) + xcd
-      p = ((b / kRound) * 8 + (w & 7)) * kChunk + (w >> 3);
-    }
-    const int full = tiles / kChunk, rowlen = n * kChunk;
-    int c, k, r;
-    if (p < full * rowlen) {
-      int rem;
-      divmod((unsigned)p, (unsigned)rowlen, deal.inv_rowlen, c, rem);
-      k = rem / kChunk; r = rem % kChunk;
-    } else {                                              // the short last chunk of every instance
-      const int cl = tiles - full * kChunk, pp = p - full * rowlen;
-      c = full;
-      divmod((unsigned)pp, (unsigned)cl, deal.inv_cl, k, r);
-    }
-    int turns;
-    divmod((unsigned)(k + c), (unsigned)n, deal.inv_n, turns, slot);
-    tile = c * kChunk + r;
-  } else {
-    divmod(blockIdx.x, (unsigned)tiles, deal.inv_tiles, slot, tile);
-  }
-  const int inst = t.perm[first + slot];
+  divmod(blockIdx.x, (unsigned)tiles, deal.inv_tiles, slot, tile);
+  const int inst = t.perm[first + slot].x;
   const int S = t.S, E = t.E, EP = t.EP;
   const int row = t.off[inst] + l;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, scalar
@@ -368,18 +255,7 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int 
   // NW times (from L2).
   const int wbase = (split ? tile : tile * NW + wave) * (64 * K);
   const bool present = wbase <= E;                       // else: whole wave beyond the table
-  const int n_in = (E - wbase + 1 < 64) ? E - wbase + 1 : 64;   // budgets of this wave inside the table
 
-  // The run test's words (the previous layer's M, then two summaries whose place depends on
-  // it: two memory round trips in a row) are asked for around the loads that stage the tile
-  // of R, so that the three overlap instead of following one another.
-  int rt_m = 0, rt_b1 = 0, rt_b2 = 0;
-  float rt_c = INFINITY;
-  const bool rt_lane = RUNS && present && lane < S;
-  if (rt_lane) {
-    rt_m = t.M[(size_t)(row - 1) * S + lane];
-    if (FIRST) rt_c = t.c[(size_t)(row - 1) * S + lane];
-  }
   {
     const float4* __restrict__ src = reinterpret_cast<const float4*>(t.Rt + (size_t)row * S * RS);
     constexpr int NSTG = (SP * RQ + 64 * NW - 1) / (64 * NW);
@@ -389,18 +265,6 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int 
       const int i = threadIdx.x + k * 64 * NW;
       stg[k] = (i < S * RQ) ? src[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
-    if (rt_lane && !FIRST) {
-      const int m = (rt_m < 0 || rt_m > E + 1) ? E + 1 : rt_m;
-      const int e_last = wbase + n_in - 1;
-      if (e_last >= m) {                                 // else: +inf throughout
-        // the words of the (at most two) groups that this wave's budgets fall in; the run test
-        // is decided without them where the column starts inside the wave (wbase < m), but the
-        // dense path wants them there too
-        const float* __restrict__ sp_ = sum_table(t, inst, row - 1, l - 1) + (size_t)lane * (EP >> 6);
-        rt_b1 = __float_as_int(sp_[(wbase > m ? wbase - m : 0) >> 6]);
-        rt_b2 = __float_as_int(sp_[(e_last - m) >> 6]);
-      }
-    }
 #pragma unroll
     for (int k = 0; k < NSTG; ++k) {
       const int i = threadIdx.x + k * 64 * NW;
@@ -408,96 +272,18 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int 
     }
   }
   __syncthreads();
-  if (!RUNS && !present) return;
+  if (!present) return;
   const int s_begin = split ? (wave * S) / NW : 0;
   const int s_end = split ? ((wave + 1) * S) / NW : S;
   const float* __restrict__ Cp = c_table(t, inst, row - 1, l - 1);
   float* __restrict__ Cn = c_table(t, inst, row, l);
   uint8_t* __restrict__ An = ARG ? t.A + (size_t)row * S * EP : nullptr;
-  // group records: kept beside A whenever the context uses the run shortcut, by split launches
-  // too (the pointer is formed where it is used: it would stay live across the row loop)
-  constexpr bool GROUPS = ARG && (RUNS || SPLIT);
   const int e0 = wbase + lane;
-
-  // Summaries: besides its table every layer leaves, per strategy and per group of 64 budgets
-  // e' of its min-plus product, the value T + c if all 64 are equal and NaN if not (sum_cur).
-  // With the run shortcut the next layer reads those few words first: column s' of its input
-  // over the wave's budgets [wbase, e_last] is C_{l-1}[s'][e] = +inf below M(l-1, s') and the
-  // previous layer's T + c at e - M above, which spans at most two of its groups; the column
-  // is constant if both summaries are the same number.  If every column is, the wave takes
-  // uniform_tile and never loads the table; otherwise it loads it and computes every cell.
-  // The layer-1 launch tests layer 0's closed form at the two ends (the columns are monotone).
-  const bool want_sum = RUNS ? true : (SPLIT ? t.runs != 0 : false);
-  // A split launch writes every cell, so NaN in all its words is as good as the true words
-  // for every reader; the true ones only help a later unsplit launch to recognise runs, which
-  // happens in the partition search (runs == 2) and never inside one solve (launches shrink).
-  const bool true_sum = RUNS ? true : (SPLIT ? t.runs == 2 : false);
-  float* __restrict__ sum_cur = want_sum ? sum_table(t, inst, row, l) : nullptr;
-  if (RUNS) {
-    static_assert(!RUNS || (K == 1 && SP <= 64), "one budget per lane, one lane per strategy");
-    const int e_last = wbase + n_in - 1;
-    bool ok = true;
-    float v = INFINITY;
-    if (rt_lane) {
-      const int m = (rt_m < 0 || rt_m > E + 1) ? E + 1 : rt_m;
-      if (FIRST) {
-        const float cv = rt_c;
-        v = wbase >= m ? cv : INFINITY;
-        const float hi = e_last >= m ? cv : INFINITY;
-        ok = __float_as_int(v) == __float_as_int(hi);
-      } else if (e_last < m) {
-        // the whole range lies in the +inf prefix
-      } else if (wbase < m) {
-        ok = false;
-      } else {
-        ok = rt_b1 == rt_b2 && !is_nan_bits(rt_b1);
-        v = __int_as_float(rt_b1);
-      }
-    }
-    const bool mine = __builtin_amdgcn_ballot_w64(!ok) == 0;
-    // Do all waves of the workgroup (those inside the table) carry the same one column?  Each
-    // publishes its verdict and its column, and every wave forms the same answer from them.
-    static_assert(!RUNS || NW == 4, "four waves share their columns");
-    __shared__ float x_col[NW][64];
-    __shared__ int x_ok[NW];
-    x_col[wave][lane] = v;
-    if (lane == 0) x_ok[wave] = present ? (mine ? 1 : 0) : 2;       // 2: not inside the table
-    __syncthreads();
-    const float v0 = x_col[0][lane];
-    bool same = true;
-    int inside = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const int st = x_ok[w];
-      same = same && (st == 2 || (st == 1 && __float_as_int(x_col[w][lane]) == __float_as_int(v0)));
-      inside += (st != 2) ? 1 : 0;
-    }
-    if (__builtin_amdgcn_ballot_w64(!same) == 0) {
-      // one wave does it, a lane per output strategy: the loop over the candidates is as long
-      // for eleven lanes as for all of them, and the other three leave their issue slots to
-      // the waves that compute cell by cell
-      if (wave == 0)
-        wide_tile<SP, ARG>(v0, rt_lds, 0, S, lane, tile * NW * 64, Cn,
-                           GROUPS ? group_records(t, row) : nullptr, sum_cur, E, EP, counts, inside);
-      return;
-    }
-    if (!present) return;
-    if (mine) {
-      uniform_tile<SP, ARG>(v, rt_lds, s_begin, s_end, lane, e0, wbase, Cn,
-                            GROUPS ? group_records(t, row) : nullptr, sum_cur, E, EP, counts ? counts + 1 : nullptr);
-      return;
-    }
-  }
-  int sumv = kNaNBits;                                    // lane j: summary of strategy s_begin + j
 
   // EP is a multiple of 64*K and wbase <= E < EP, so rows e0 + 64*j < EP are
   // inside the allocation; rows in (E, EP) are padding whose results are
   // never stored into the table proper.
   float cp[K][SP];
-  // the table values are formed here, after the run test, not before it (they would stay live
-  // across the run paths otherwise)
-  int e0d = e0;
-  asm volatile("" : "+v"(e0d));
   if (FIRST) {
     // l == 1: layer 0 is a closed form, C(0, e, s') = e >= M(0, s') ? c(0, s') : +inf,
     // built here instead of being written to and read back from HBM.
@@ -510,78 +296,8 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int 
       const int mv = col ? m0[sp] : 0;
 #pragma unroll
       for (int j = 0; j < K; ++j) {
-        const int e = e0d + 64 * j;
+        const int e = e0 + 64 * j;
         cp[j][sp] = (mv >= 0 && e >= mv && e <= E) ? cv : INFINITY;
-      }
-    }
-  } else if (RUNS) {
-    // With summaries the previous layer's cells are written only where their group's word is
-    // NaN (see table_cell); below M(l-1, s') the cell is +inf.  The words of this wave's groups
-    // are already here, in the lane of their column (the run test asked for them): the cell is
-    // loaded whatever it holds, and the word wins where it is a number.
-    static_assert(K == 1, "one budget per lane");
-#pragma unroll
-    for (int sp = 0; sp < SP; ++sp) {
-      float c = INFINITY;
-      if (sp < SP - 3 || sp < S) c = __builtin_nontemporal_load(&Cp[(size_t)sp * EP + e0d]);
-      cp[0][sp] = c;
-    }
-#pragma unroll
-    for (int sp = 0; sp < SP; ++sp) {
-      if (sp < SP - 3 || sp < S) {
-        const int m_raw = __builtin_amdgcn_readlane(rt_m, sp);
-        const int m = (m_raw < 0 || m_raw > E + 1) ? E + 1 : m_raw;
-        const int b1 = __builtin_amdgcn_readlane(rt_b1, sp), b2 = __builtin_amdgcn_readlane(rt_b2, sp);
-        // the first budget of the second group; which word is a number is known per wave
-        const int thr = m + ((((wbase > m ? wbase - m : 0) >> 6) + 1) << 6);
-        const float v1 = is_nan_bits(b1) ? cp[0][sp] : __int_as_float(b1);
-        const float v2 = is_nan_bits(b2) ? cp[0][sp] : __int_as_float(b2);
-        cp[0][sp] = e0d < m ? INFINITY : e0d < thr ? v1 : v2;
-      }
-    }
-  } else if (SPLIT && t.runs != 0 && !t.prev_full) {
-    // A split launch whose input came from an unsplit one with the run shortcut, or from an
-    // unknown launch (the partition search's kept tables): the same rule, but no words at
-    // hand.  (A split launch that follows a split launch finds every cell written and takes
-    // the plain loads below.)
-    static_assert(K == 1, "one budget per lane");
-    const float* __restrict__ Tp = sum_table(t, inst, row - 1, l - 1);
-    // lane s' holds M(l-1, s')
-    const int mprev = (lane < S) ? t.M[(size_t)(row - 1) * S + lane] : 0;
-    // First the summaries of all columns, into the registers of the table values.  Then one
-    // more load per column from an address chosen by what came: the cell where the word is
-    // NaN, the word once more where it is a number (a cache hit).  No branch, so the loads of
-    // the second round go out back to back, and never two values per column in registers
-    // (asking for word and cell of every column at once takes 2 SP registers; a branch around
-    // each cell's load makes every one of them a round trip of its own).
-#pragma unroll
-    for (int sp = 0; sp < SP; ++sp) {
-      float w = INFINITY;
-      if (sp < SP - 3 || sp < S) {
-        const int m_raw = __builtin_amdgcn_readlane(mprev, sp);
-        const int m = (m_raw < 0 || m_raw > E + 1) ? E + 1 : m_raw;
-        const int idx = e0d - m;
-        w = Tp[(size_t)sp * (EP >> 6) + ((idx > 0 ? idx : 0) >> 6)];
-      }
-      cp[0][sp] = w;
-    }
-#pragma unroll
-    for (int sp = 0; sp < SP; ++sp) {
-      if (sp < SP - 3 || sp < S) {
-        const int m_raw = __builtin_amdgcn_readlane(mprev, sp);
-        const int m = (m_raw < 0 || m_raw > E + 1) ? E + 1 : m_raw;
-        const int idx = e0d - m;
-        const float* again = &Tp[(size_t)sp * (EP >> 6) + ((idx > 0 ? idx : 0) >> 6)];
-        const float* cell = &Cp[(size_t)sp * EP + e0d];
-        cp[0][sp] = *(is_nan_bits(__float_as_int(cp[0][sp])) ? cell : again);
-      }
-    }
-#pragma unroll
-    for (int sp = 0; sp < SP; ++sp) {
-      if (sp < SP - 3 || sp < S) {
-        const int m_raw = __builtin_amdgcn_readlane(mprev, sp);
-        const int m = (m_raw < 0 || m_raw > E + 1) ? E + 1 : m_raw;
-        cp[0][sp] = e0d < m ? INFINITY : cp[0][sp];
       }
     }
   } else {
@@ -592,41 +308,10 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int 
         {
         // a large launch reads every table value exactly once: streaming loads leave the
         // caches to the stores; a split launch is small enough to find its table in cache
-        const float* src = &Cp[(size_t)sp * EP + e0d + 64 * j];
+        const float* src = &Cp[(size_t)sp * EP + e0 + 64 * j];
         cp[j][sp] = !(sp < SP - 3 || sp < S) ? INFINITY : SPLIT ? *src : __builtin_nontemporal_load(src);
       }
     }
-  }
-
-  if (RUNS) {
-    // The summaries speak for whole groups of 64 budgets of the previous layer's product, and a
-    // column of this wave lies across two of them: about half of the waves that arrive here
-    // have 64 equal columns after all, as the loaded values show.  They take the run path too,
-    // with the column put together from the first lane's values.
-    bool differs = false;
-#pragma unroll
-    for (int sp = 0; sp < SP; ++sp) {
-      const int b = __float_as_int(cp[0][sp]);
-      differs = differs || (b != __builtin_amdgcn_readfirstlane(b));
-    }
-    if (__builtin_amdgcn_ballot_w64(differs && e0 <= E) == 0) {
-      float colv = INFINITY;
-#pragma unroll
-      for (int sp = 0; sp < SP; ++sp) {
-        const int f = __builtin_amdgcn_readfirstlane(__float_as_int(cp[0][sp]));
-        colv = (lane == sp) ? __int_as_float(f) : colv;
-      }
-      uniform_tile<SP, ARG>(colv, rt_lds, s_begin, s_end, lane, e0, wbase, Cn,
-                            GROUPS ? group_records(t, row) : nullptr, sum_cur, E, EP, counts ? counts + 2 : nullptr);
-      return;
-    }
-  }
-
-  // this wave's records will be in A, whatever its summary words say (said here, before the row
-  // loop, where registers are free)
-  if (GROUPS) {
-    uint8_t* __restrict__ Ag = group_records(t, row);
-    if (Ag && s_begin + lane < s_end) Ag[(size_t)(s_begin + lane) * (EP >> 6) + (wbase >> 6)] = (uint8_t)kNoGroupRecord;
   }
 
   if (!ARG) {
@@ -634,24 +319,13 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int 
     // one record they need per layer from the kept tables).  One add and half a
     // three-input min per candidate; the R row is consumed quad by quad as it arrives.
     static_assert(K == 1 || ARG, "the values-only path handles one budget per lane");
-    float4 rowq[PRE ? PD : 1];
-    if (PRE) {
-#pragma unroll
-      for (int q = 0; q < PD; ++q) rowq[q] = rt_lds[s_begin * RQ + (q < RQ ? q : RQ - 1)];
-    }
 #pragma unroll 1
     for (int s = s_begin; s < s_end; ++s) {
       float acc = INFINITY, cs = 0.0f;
       int m_raw = 0;
-      const int s_next = (s + 1 < s_end) ? s + 1 : s;      // the last row is fetched once more, unused
 #pragma unroll
-      for (int q = 0; q < (PRE ? RQP : RQ); ++q) {
-        float4 v;
-        if (PRE) {
-          const int nq = q + PD, qq = nq < RQP ? nq : nq - RQP;
-          v = rowq[q % PD];
-          rowq[q % PD] = rt_lds[(nq < RQP ? s : s_next) * RQ + (qq < RQ ? qq : RQ - 1)];
-        } else v = rt_lds[s * RQ + q];
+      for (int q = 0; q < RQ; ++q) {
+        const float4 v = rt_lds[s * RQ + q];
         const float rq[4] = {v.x, v.y, v.z, v.w};
         float xq[4];
 #pragma unroll
@@ -672,28 +346,15 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int 
       const __amdgpu_buffer_rsrc_t binf = __builtin_amdgcn_make_buffer_rsrc(Cs, 0, m * 4, kBufWord3);
       const int outb = __float_as_int(acc + cs);
       __builtin_amdgcn_raw_buffer_store_b32((unsigned)outb, bc, (e0 + m) * 4, 0, 0);
-      if (!RUNS && wbase < m)                              // wave-uniform: some lane is below M (with
-        __builtin_amdgcn_raw_buffer_store_b32(0x7f800000u, binf, e0 * 4, 0, 0);   // the run shortcut the readers know)
-      if (true_sum) {
-        // T + c is non-increasing along the budgets: all equal exactly when the ends are
-        const int first = __builtin_amdgcn_readfirstlane(outb), last = __builtin_amdgcn_readlane(outb, n_in - 1);
-        sumv = (lane == s - s_begin) ? (first == last ? first : kNaNBits) : sumv;
-      }
+      if (wbase < m)                                       // wave-uniform: some lane is below M
+        __builtin_amdgcn_raw_buffer_store_b32(0x7f800000u, binf, e0 * 4, 0, 0);
     }
-    if (want_sum && s_begin + lane < s_end)
-      sum_cur[(size_t)(s_begin + lane) * (EP >> 6) + (wbase >> 6)] = __int_as_float(sumv);
     return;
   }
 
   static_assert(K == 1, "one budget per lane");
-  float4 rowq[PRE ? PD : 1];
-  if (PRE) {
-#pragma unroll
-    for (int q = 0; q < PD; ++q) rowq[q] = rt_lds[s_begin * RQ + (q < RQ ? q : RQ - 1)];
-  }
 #pragma unroll 1
   for (int s = s_begin; s < s_end; ++s) {
-    const int s_next = (s + 1 < s_end) ? s + 1 : s;        // the last row is fetched once more, unused
     // ---- value pass, streaming: the R row is consumed quad by quad as it arrives from LDS,
     // candidates fold into chunk minima and those into the prefix minima at once, so that
     // only the prefix minima stay live (the sums are not kept: the rescan redoes the few it
@@ -703,13 +364,8 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int 
     float cs = 0.0f;
     int m_raw = 0;
 #pragma unroll
-    for (int q = 0; q < (PRE ? RQP : RQ); ++q) {
-      float4 v;
-      if (PRE) {
-        const int nq = q + PD, qq = nq < RQP ? nq : nq - RQP;
-        v = rowq[q % PD];
-        rowq[q % PD] = rt_lds[(nq < RQP ? s : s_next) * RQ + (qq < RQ ? qq : RQ - 1)];
-      } else v = rt_lds[s * RQ + q];
+    for (int q = 0; q < RQ; ++q) {
+      const float4 v = rt_lds[s * RQ + q];
       const float rq[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
@@ -792,23 +448,18 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_minplus(Tables t, int l, int 
       __builtin_amdgcn_raw_buffer_store_b8((unsigned char)arg, ba, e, 0, SPLIT ? 0 : kStreaming);
       const int outb = __float_as_int(T + cs);
       __builtin_amdgcn_raw_buffer_store_b32((unsigned)outb, bc, (e + m) * 4, 0, 0);
-      if (!RUNS && wbase + 64 * j < m)                   // wave-uniform: some lane is below M (with
-        __builtin_amdgcn_raw_buffer_store_b32(0x7f800000u, binf, e * 4, 0, 0);    // the run shortcut the readers know)
-      if (true_sum) {
-        const int first = __builtin_amdgcn_readfirstlane(outb), last = __builtin_amdgcn_readlane(outb, n_in - 1);
-        sumv = (lane == s - s_begin) ? (first == last ? first : kNaNBits) : sumv;
-      }
+      if (wbase + 64 * j < m)                            // wave-uniform: some lane is below M
+        __builtin_amdgcn_raw_buffer_store_b32(0x7f800000u, binf, e * 4, 0, 0);
     }
   }
-  if (want_sum && s_begin + lane < s_end)
-    sum_cur[(size_t)(s_begin + lane) * (EP >> 6) + (wbase >> 6)] = __int_as_float(sumv);
+  }
 }
 
 // Any S up to 256 (used above 128): the C_{l-1} tile of 64 budgets is staged in LDS as
 // [S][64]; wave w handles output strategies w, w+4, ...
 __global__ __launch_bounds__(256) void k_minplus_generic(Tables t, int l, int tiles, int first) {
   extern __shared__ float lds[];
-  const int inst = t.perm[first + blockIdx.x / tiles];
+  const int inst = t.perm[first + blockIdx.x / tiles].x;
   const int tile = blockIdx.x % tiles;
   const int S = t.S, RS = t.RS, E = t.E, EP = t.EP;
   const int row = t.off[inst] + l;
@@ -857,26 +508,49 @@ struct Blocking {                       // budgets per lane for a given strategy
   static constexpr int MINW_FIRST = (SP > 40 && SP <= 44) ? 7 : MINW;
   // without the argmin pass: the SP table values plus about 16 working registers
   static constexpr int MINW_VALUES = (SP <= 44) ? 8 : (SP <= 52) ? 7 : (SP <= 60) ? 6 : (SP <= 64) ? 5 : (SP <= 96) ? 4 : 3;
-  // with the run shortcut compiled in: the summaries, the exchange, the second look at the
-  // loaded columns and (up to 56 strategies) four quads of R in flight ahead of the fold (see
-  // PRE in the kernel) take a few registers more; targets found by compiling every size.  The
-  // values-only kernels would fit one wave more at some sizes; measured, that is no gain
-  // (S=44: 7 waves 1.80 ms per solve, 5 or 4 waves 1.76).
-  static constexpr int MINW_RUNS = (SP <= 24) ? 8 : (SP == 32) ? 6 : (SP <= 36) ? 7 : (SP <= 40) ? 6 : 5;   // (32: 7 spills four registers)
-  static constexpr int MINW_VALUES_RUNS = (SP <= 24) ? 8 : (SP <= 28) ? 7 : (SP <= 32) ? 6 : (SP <= 40) ? 5
-                                          : (SP <= 52) ? 4 : (SP <= 56) ? 3 : 5;
+  // the pruned step: up to 32 KB of LDS per workgroup leave five workgroups per compute unit
+  // (at four waves per SIMD beside it the layer-1 variant would spill two registers less than none)
+  static constexpr int MINW_RUNS = 5, MINW_RUNS_FIRST = 4;
 };
 
+// The shape of a pruned launch: groups of 64 budgets per wave and workgroups per instance.
+struct PrunedShape { int unit, places; size_t lds; };
+static PrunedShape pruned_shape(const Tables& t, int n_active) {
+  const int groups = (t.E + 64) / 64;
+  PrunedShape p;
+  const long long all = (long long)groups * n_active;
+  p.unit = (t.counts || all >= 16384) ? kUnit : all >= 4096 ? 1 : 0;
+  p.places = p.unit == 0 ? groups : (groups + kWaves * p.unit - 1) / (kWaves * p.unit);
+  p.lds = (size_t)pruned_lds_floats(t.S, kept(t.SP)) * sizeof(float);
+  return p;
+}
+
 template <int SP>
-static void launch_minplus_sp(const Tables& t_in, int l, int first, int n_active, int n_prev, hipStream_t st) {
+static void launch_minplus_sp(const Tables& t, int l, int first, int n_active, hipStream_t st) {
   constexpr int K = Blocking<SP>::K, NW = Blocking<SP>::NW, CH = Blocking<SP>::CH,
                 MINW = Blocking<SP>::MINW;
-  Tables t = t_in;
+  if (t.runs != 0) {
+    static_assert(NW == kWaves, "the pruned step's workgroup");
+    constexpr int MR = Blocking<SP>::MINW_RUNS, MR1 = Blocking<SP>::MINW_RUNS_FIRST;
+    const PrunedShape p = pruned_shape(t, n_active);
+#define GBMW_LAUNCH(MW, FIRST_, ARG_, COUNT_)                                                                  \
+  hipLaunchKernelGGL((k_minplus<SP, K, NW, CH, MW, FIRST_, ARG_, false, true, COUNT_>),                        \
+                     dim3((unsigned)p.places * n_active), dim3(64 * NW), p.lds, st, t, l, p.places, first,     \
+                     make_deal(p.places, n_active, p.unit))
+    if (t.counts) {                                      // the counting twin
+      if (t.A == nullptr) { if (l == 1) GBMW_LAUNCH(2, true, false, true); else GBMW_LAUNCH(2, false, false, true); }
+      else { if (l == 1) GBMW_LAUNCH(2, true, true, true); else GBMW_LAUNCH(2, false, true, true); }
+    } else if (t.A == nullptr) {
+      if (l == 1) GBMW_LAUNCH(MR1, true, false, false); else GBMW_LAUNCH(MR, false, false, false);
+    } else {
+      if (l == 1) GBMW_LAUNCH(MR1, true, true, false); else GBMW_LAUNCH(MR, false, true, false);
+    }
+#undef GBMW_LAUNCH
+    return;
+  }
   int tiles = (t.E + 1 + 64 * K * NW - 1) / (64 * K * NW);
   // fewer than two and a half workgroups per compute unit: split the strategies over the waves
   const int split = ((long long)tiles * n_active < 640) ? 1 : 0;
-  // did the launch that produced this one's input split too (and so write every cell)?
-  t.prev_full = (n_prev < 0 || (n_prev > 0 && (long long)tiles * n_prev < 640)) ? 1 : 0;
   if (split) tiles = (t.E + 1 + 64 * K - 1) / (64 * K);
   constexpr int RS = (SP + 2 + 3) / 4 * 4;
   const dim3 grid((unsigned)tiles * n_active), block(64 * NW);
@@ -884,48 +558,50 @@ static void launch_minplus_sp(const Tables& t_in, int l, int first, int n_active
   // Split launches are the small ones, where a wave's own latency counts and registers are
   // plentiful: a low occupancy target lets the compiler keep the whole R row in flight.
   constexpr int MS = Blocking<SP>::MINW_SPLIT;
-#define GBMW_LAUNCH(MW, FIRST_, ARG_, SPLIT_, RUNS_)                                                        \
-  hipLaunchKernelGGL((k_minplus<SP, K, NW, CH, MW, FIRST_, ARG_, SPLIT_, RUNS_>), grid, block, lds, st, t, l, \
+#define GBMW_LAUNCH(MW, FIRST_, ARG_, SPLIT_)                                                               \
+  hipLaunchKernelGGL((k_minplus<SP, K, NW, CH, MW, FIRST_, ARG_, SPLIT_, false>), grid, block, lds, st, t, l, \
                      tiles, first, make_deal(tiles, n_active))
-  const bool runs = t.runs != 0;
-  if (runs && !split && t.counts) {                      // the counting twin of the unsplit run-shortcut kernels
-#define GBMW_LAUNCH_COUNT(FIRST_, ARG_)                                                                      \
-  hipLaunchKernelGGL((k_minplus<SP, K, NW, CH, 2, FIRST_, ARG_, false, true, true>), grid, block, lds, st, t, l, \
-                     tiles, first, make_deal(tiles, n_active))
-    if (t.A == nullptr) { if (l == 1) GBMW_LAUNCH_COUNT(true, false); else GBMW_LAUNCH_COUNT(false, false); }
-    else { if (l == 1) GBMW_LAUNCH_COUNT(true, true); else GBMW_LAUNCH_COUNT(false, true); }
-#undef GBMW_LAUNCH_COUNT
-    return;
-  }
   if (t.A == nullptr) {
-    constexpr int MW = Blocking<SP>::MINW_VALUES, MWR = Blocking<SP>::MINW_VALUES_RUNS;
-    if (l == 1) {
-      if (split) GBMW_LAUNCH(MS, true, false, true, false);
-      else if (runs) GBMW_LAUNCH(MWR, true, false, false, true);
-      else GBMW_LAUNCH(MW, true, false, false, false);
-    } else {
-      if (split) GBMW_LAUNCH(MS, false, false, true, false);
-      else if (runs) GBMW_LAUNCH(MWR, false, false, false, true);
-      else GBMW_LAUNCH(MW, false, false, false, false);
-    }
+    constexpr int MW = Blocking<SP>::MINW_VALUES;
+    if (l == 1) { if (split) GBMW_LAUNCH(MS, true, false, true); else GBMW_LAUNCH(MW, true, false, false); }
+    else { if (split) GBMW_LAUNCH(MS, false, false, true); else GBMW_LAUNCH(MW, false, false, false); }
   } else {
-    constexpr int M1 = Blocking<SP>::MINW_FIRST, MR = Blocking<SP>::MINW_RUNS;
-    if (l == 1) {
-      if (split) GBMW_LAUNCH(MS, true, true, true, false);
-      else if (runs) GBMW_LAUNCH(MR, true, true, false, true);
-      else GBMW_LAUNCH(M1, true, true, false, false);
-    } else {
-      if (split) GBMW_LAUNCH(MS, false, true, true, false);
-      else if (runs) GBMW_LAUNCH(MR, false, true, false, true);
-      else GBMW_LAUNCH(MINW, false, true, false, false);
-    }
+    constexpr int M1 = Blocking<SP>::MINW_FIRST;
+    if (l == 1) { if (split) GBMW_LAUNCH(MS, true, true, true); else GBMW_LAUNCH(M1, true, true, false); }
+    else { if (split) GBMW_LAUNCH(MS, false, true, true); else GBMW_LAUNCH(MINW, false, true, false); }
+  }
+#undef GBMW_LAUNCH
+}
+
+// The pruned step beyond 64 strategies: a lane holds NCH columns (and NCH outputs).
+template <int NCH, bool FIRST, bool ARG, bool COUNT>
+__global__ __launch_bounds__(64 * kWaves, NCH == 2 ? 4 : 3) void k_pruned_wide(Tables t, int l, int places, int first, Deal deal) {
+  extern __shared__ float pruned_lds[];
+  int place, slot;
+  divmod(blockIdx.x, (unsigned)deal.n, deal.inv_n, place, slot);
+  pruned_step<NCH, (COUNT ? 4 : kept(64 * NCH)), FIRST, ARG, COUNT>(t, l, t.perm[first + slot], place, places, deal.unit, pruned_lds);
+}
+
+template <int NCH>
+static void launch_pruned_wide(const Tables& t, int l, int first, int n_active, hipStream_t st) {
+  const PrunedShape p = pruned_shape(t, n_active);
+#define GBMW_LAUNCH(FIRST_, ARG_, COUNT_)                                                                      \
+  hipLaunchKernelGGL((k_pruned_wide<NCH, FIRST_, ARG_, COUNT_>), dim3((unsigned)p.places * n_active),          \
+                     dim3(64 * kWaves), p.lds, st, t, l, p.places, first, make_deal(p.places, n_active, p.unit))
+  if (t.counts) {
+    if (t.A == nullptr) { if (l == 1) GBMW_LAUNCH(true, false, true); else GBMW_LAUNCH(false, false, true); }
+    else { if (l == 1) GBMW_LAUNCH(true, true, true); else GBMW_LAUNCH(false, true, true); }
+  } else if (t.A == nullptr) {
+    if (l == 1) GBMW_LAUNCH(true, false, false); else GBMW_LAUNCH(false, false, false);
+  } else {
+    if (l == 1) GBMW_LAUNCH(true, true, false); else GBMW_LAUNCH(false, true, false);
   }
 #undef GBMW_LAUNCH
 }
 
 // 65 to 128 strategies: the same register-blocked kernel, every lane with its S' table values
 // in registers (148 to 168 of them at 128 strategies: three waves per SIMD), in larger workgroups
-// (see Blocking::NW).  No run shortcut, no split shape, layer 0 read from memory.
+// (see Blocking::NW).  No split shape, layer 0 read from memory.
 template <int SP>
 static void launch_minplus_big(const Tables& t, int l, int first, int n_active, hipStream_t st) {
   constexpr int NW = Blocking<SP>::NW, CH = Blocking<SP>::CH;
@@ -941,10 +617,15 @@ static void launch_minplus_big(const Tables& t, int l, int first, int n_active, 
                        l, tiles, first, make_deal(tiles, n_active));
 }
 
-void launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t st, int n_prev) {
+void launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t st) {
   if (n_active <= 0) return;
+  if (t.runs != 0 && t.S > 64) {
+    if (t.S <= 128) launch_pruned_wide<2>(t, l, first, n_active, st);
+    else launch_pruned_wide<4>(t, l, first, n_active, st);
+    return;
+  }
   switch (t.SP) {
-#define GBMW_CASE(N) case N: launch_minplus_sp<N>(t, l, first, n_active, n_prev, st); return;
+#define GBMW_CASE(N) case N: launch_minplus_sp<N>(t, l, first, n_active, st); return;
     GBMW_CASE(4) GBMW_CASE(8) GBMW_CASE(12) GBMW_CASE(16) GBMW_CASE(20) GBMW_CASE(24)
     GBMW_CASE(28) GBMW_CASE(32) GBMW_CASE(36) GBMW_CASE(40) GBMW_CASE(44) GBMW_CASE(48)
     GBMW_CASE(52) GBMW_CASE(56) GBMW_CASE(60) GBMW_CASE(64)
@@ -963,10 +644,20 @@ void launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t
                      (size_t)t.S * 64 * sizeof(float), st, t, l, tiles, first);
 }
 
-bool layer0_in_registers(int S) { return S <= 64; }
+bool layer0_in_registers(const Tables& t) { return t.runs != 0 || t.S <= 64; }
 
-bool launch_is_split(const Tables& t, int n_active) {
-  return t.S <= 64 && (long long)((t.E + 256) / 256) * n_active < 640;
+// When the pruned step is taken (else the dense kernels; the results are the same).  S == 256: a
+// strategy index of 255 would read as kNoGroupRecord.  Beyond 64 strategies always (the dense kernels
+// take 13 times as long at B=16, S=128, E=32768 and 3 times at B=4, S=186, E=16384).  Up to 64 it
+// takes 10 to 17 us per layer however small the launch is (a chain of memory round trips per group),
+// a split dense launch about 10 us plus its updates at 1.75e13 per second: they meet at about 4e8
+// updates per layer (B=37, S=21, E=4999, 8e7 updates: 276 us per solve pruned, 228 dense; B=64, S=44,
+// E=32768, 4e9: 0.85 ms and 3.2 ms).  Launches that the dense kernels would not split are larger in
+// groups and take it too.
+bool pruned_step_takes(int S, int E, int n, long long most_dense_updates) {
+  if (S >= 256) return false;
+  if (S > 64) return true;
+  return (long long)((E + 256) / 256) * n >= 640 || (long long)n * (E + 1) * S * S >= most_dense_updates;
 }
 
 const char* minplus_variant(int S) {
@@ -978,46 +669,13 @@ const char* minplus_variant(int S) {
 // final reduce: best(e) = min_s C(L_b - 1, e, s), lowest-index argmin
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_final(Tables t, int first) {
-  const int inst = t.perm[first + blockIdx.y];
+  const int inst = t.perm[first + blockIdx.y].x;
   const int e = t.final_from + blockIdx.x * 256 + threadIdx.x;
   if (e > t.E) return;
   const int l = t.L[inst] - 1;
   const float* __restrict__ C = c_table(t, inst, t.off[inst] + l, l);
   float b = INFINITY;
   int a = 0;
-  if (t.runs != 0) {
-    // the summaries stand for the cells of their groups where they are numbers (table_cell)
-    const float* __restrict__ Ts = sum_table(t, inst, t.off[inst] + l, l);
-    const int* __restrict__ Ml = t.M + (size_t)(t.off[inst] + l) * t.S;
-    int s = 0;
-    for (; s + 8 <= t.S; s += 8) {
-      float x[8], w[8];
-      int idx[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int m = Ml[s + i];
-        idx[i] = (m < 0) ? -1 : e - m;
-        w[i] = Ts[(size_t)(s + i) * (t.EP >> 6) + ((idx[i] > 0 ? idx[i] : 0) >> 6)];
-      }
-      // the cell is asked for only where its group's word does not stand for it (most groups
-      // of a step-function table are runs: their cells were never written and need not be read)
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        x[i] = (idx[i] >= 0 && is_nan_bits(__float_as_int(w[i]))) ? C[(size_t)(s + i) * t.EP + e] : w[i];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float v = idx[i] < 0 ? INFINITY : x[i];
-        if (v < b) { b = v; a = s + i; }
-      }
-    }
-    for (; s < t.S; ++s) {
-      const float v = table_cell(t, C, Ts, Ml, s, e);
-      if (v < b) { b = v; a = s; }
-    }
-    t.best[(size_t)inst * t.EP + e] = b;
-    t.best_s[(size_t)inst * t.EP + e] = (uint8_t)a;
-    return;
-  }
   // eight loads in flight, then the compares in strategy order
   int s = 0;
   for (; s + 8 <= t.S; s += 8) {
@@ -1036,8 +694,85 @@ __global__ __launch_bounds__(256) void k_final(Tables t, int first) {
   t.best_s[(size_t)inst * t.EP + e] = (uint8_t)a;
 }
 
+// The same from the summaries: a wave takes up to four groups of 64 budgets, a lane per column, and
+// where the columns that can be the smallest are constant the group's minimum is one number;
+// elsewhere their cells are read (the bounds are those of the layer step with R = 0).
+template <int NCH>
+__global__ __launch_bounds__(256) void k_final_pruned(Tables t, int first, int unit) {
+  const int inst = t.perm[first + blockIdx.y].x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int base = t.final_from + (int)(blockIdx.x * 4 + wave) * unit * 64;
+  const int S = t.S, E = t.E, EP = t.EP;
+  if (base > E) return;
+  const int l = t.L[inst] - 1, row = t.off[inst] + l;
+  const float* __restrict__ C = c_table(t, inst, row, l);
+  Columns<NCH> q;
+  float2 w[NCH][kUnit + 1];
+  load_unit<NCH>(t, sum_table(t, inst, row, l), t.M + (size_t)row * S, base, unit, lane, q.m, w);
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) q.rl[c] = make_float2(0.0f, 0.0f);
+#pragma unroll
+  for (int g = 0; g < kUnit; ++g) {
+    const int wb = base + 64 * g;
+    if (g >= unit || wb > E) break;
+    const int el = wb + 63 < E ? wb + 63 : E;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) { q.a[c] = w[c][g]; q.b[c] = w[c][g + 1]; }
+    float ub[NCH], lb[NCH];
+    unsigned long long cand[NCH];
+    bool varies;
+    bounds<NCH>(q, wb, el, ub, lb, cand, varies);
+    float b = INFINITY;
+    int a = 0;
+    if (!varies) {
+#pragma unroll
+      for (int c = NCH - 1; c >= 0; --c) {
+        if (cand[c] == 0) continue;
+        const bool in = (cand[c] >> lane) & 1;
+        const float v = wave_min(in ? ub[c] : INFINITY);
+        if (v <= b) { b = v; a = 64 * c + __builtin_ctzll(__builtin_amdgcn_ballot_w64(in && ub[c] == v)); }
+      }
+    } else {
+      constexpr int NB = 8;
+      const int at = wb + lane <= E ? wb + lane : E;     // final_from need not be a multiple of 64
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        unsigned long long mask = cand[c];
+        while (mask) {
+          int k[NB];
+          float cell[NB];
+#pragma unroll
+          for (int i = 0; i < NB; ++i) {                 // past the end: the last one again (no strict minimum)
+            k[i] = mask ? __builtin_ctzll(mask) : k[i > 0 ? i - 1 : 0];
+            mask &= mask - 1;
+            cell[i] = C[(size_t)(64 * c + k[i]) * EP + at];
+          }
+#pragma unroll
+          for (int i = 0; i < NB; ++i) {
+            const float x = column_value<NCH, false>(q, 64 * c + k[i], cell[i], wb, E, lane);
+            if (x < b) { b = x; a = 64 * c + k[i]; }
+          }
+        }
+      }
+    }
+    if (wb + lane <= E) {
+      t.best[(size_t)inst * EP + wb + lane] = b;
+      t.best_s[(size_t)inst * EP + wb + lane] = (uint8_t)a;
+    }
+  }
+}
+
 void launch_final(const Tables& t, int first, int count, hipStream_t st) {
   if (count <= 0) return;
+  if (t.runs != 0) {
+    const int groups = (t.E - t.final_from + 64) / 64;
+    const int unit = (long long)groups * count >= 16384 ? kUnit : 1;
+    const dim3 grid((groups + 4 * unit - 1) / (4 * unit), count);
+    if (t.S <= 64) hipLaunchKernelGGL(k_final_pruned<1>, grid, dim3(256), 0, st, t, first, unit);
+    else if (t.S <= 128) hipLaunchKernelGGL(k_final_pruned<2>, grid, dim3(256), 0, st, t, first, unit);
+    else hipLaunchKernelGGL(k_final_pruned<4>, grid, dim3(256), 0, st, t, first, unit);
+    return;
+  }
   hipLaunchKernelGGL(k_final, dim3((t.E - t.final_from + 256) / 256, count), dim3(256), 0, st, t, first);
 }
 
@@ -1264,7 +999,7 @@ __global__ __launch_bounds__(64) void k_stage_cost(Tables t, int n_stage,
         float v = c_ns[(size_t)row0 * S + s];
         for (int l = 1; l < Lb; ++l) {
           const int sn = plan[l];
-          const float r = t.Rt[((size_t)(row0 + l) * S + sn) * t.RS + s];
+          const float r = r_entry(t, row0 + l, s, sn);
           v = (v + r) + c_ns[(size_t)(row0 + l) * S + sn];
           s = sn;
         }
@@ -1341,13 +1076,13 @@ void launch_argmin_row(const Tables& t, int row, uint8_t* dst, hipStream_t st) {
 }
 
 __global__ __launch_bounds__(256) void k_export_c(Tables t, const float* __restrict__ Ctab,
-                                                  const float* __restrict__ Tsum_tab, const int* __restrict__ Mrow,
+                                                  const float2* __restrict__ Tsum_tab, const int* __restrict__ Mrow,
                                                   float* __restrict__ dst) {
   const int e = blockIdx.x * 256 + threadIdx.x, s = blockIdx.y;
   if (e > t.E) return;
   dst[(size_t)e * t.S + s] = table_cell(t, Ctab, Tsum_tab, Mrow, s, e);
 }
-void launch_export_c(const Tables& t, const float* Ctab, const float* Tsum_tab, const int* Mrow, float* dst,
+void launch_export_c(const Tables& t, const float* Ctab, const float2* Tsum_tab, const int* Mrow, float* dst,
                      hipStream_t st) {
   hipLaunchKernelGGL(k_export_c, dim3((t.E + 256) / 256, t.S), dim3(256), 0, st, t, Ctab, Tsum_tab, Mrow, dst);
 }

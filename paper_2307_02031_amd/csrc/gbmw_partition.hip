@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "gbmw_ctx.h"
+#include "gbmw_pruned.h"
 
 namespace gbmw {
 
@@ -56,9 +57,10 @@ __global__ void k_fill_u32(uint32_t* p, size_t n, uint32_t v) {
   if (i < n) p[i] = v;
 }
 
-// One workgroup per row: c and M of a model layer -> a slot row, and the layer's R straight
-// into the row's transposed table (Rt[s][s'] = R[s'][s], zero padding, then c(s) and the bits
-// of M(s): the layout the layer kernels read), so that only touched rows are prepared.
+// One workgroup per row: c and M of a model layer -> a slot row, and the layer's R, so that only
+// touched rows are prepared: as it comes with the smallest and largest entry of every row of it
+// (Rn, Row: the pruned layer step), or transposed with c(s) and the bits of M(s) riding along
+// (Rt[s][s'] = R[s'][s], zero padding: the layout the dense kernels read).
 __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ c,
                                                 const int* __restrict__ M,
                                                 const float* __restrict__ R,
@@ -66,7 +68,8 @@ __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ c,
                                                 const int* __restrict__ row_msrc,
                                                 const int* __restrict__ row_dst, int S, int SP, int RS,
                                                 float* __restrict__ c_g, int* __restrict__ M_g,
-                                                float* __restrict__ Rt,
+                                                float* __restrict__ Rt, float* __restrict__ Rn,
+                                                float4* __restrict__ Row,
                                                 const int* __restrict__ Ob, const int* __restrict__ Oms,
                                                 int* __restrict__ Ob_g, int* __restrict__ Oms_g) {
   const size_t src = (size_t)row_src[blockIdx.x], msrc = (size_t)row_msrc[blockIdx.x];
@@ -80,6 +83,12 @@ __global__ __launch_bounds__(256) void k_gather(const float* __restrict__ c,
     }
   }
   const float* __restrict__ Rl = R + src * S * S;
+  if (Rn) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int s0 = wave * 4; s0 < S; s0 += 16)
+      row_limits<4>(Rl, S, s0, lane, c + src * S, M + msrc * S, Rn + dst * S * S, Row + dst * S);
+    return;
+  }
   float* __restrict__ out = Rt + dst * S * RS;
   for (int i = threadIdx.x; i < S * RS; i += 256) {
     const int s = i / RS, sp = i % RS;
@@ -381,6 +390,15 @@ using gbmw_detail::fail;
 
 namespace {
 
+// Most rounds of a search touch a few stages only, so its launches are smaller than its number of
+// stages says: the pruned layer step pays from more updates per layer on than in one solve (32 pairs
+// of 48 layers, S=22, E=16384, 9.5e8 updates if all 120 stages are solved: 9.6 ms pruned, 8.5 ms dense;
+// S=44, E=32768, 7.6e9: 10 ms and 16.6 ms).
+bool search_takes_pruned(int S, int E, int stages) {
+  return S > 64 ? gbmw::pruned_step_takes(S, E, stages, 0)
+                : gbmw::pruned_step_takes(S, E, stages, 0) && (long long)stages * (E + 1) * S * S >= 1500000000ll;
+}
+
 struct Carver {
   char* base;
   size_t used = 0;
@@ -617,14 +635,15 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
   }
   TRY(c->d_L.reserve(sizeof(int) * B));
   TRY(c->d_off.reserve(sizeof(int) * B));
-  TRY(c->d_perm.reserve(sizeof(int) * B));
+  TRY(c->d_perm.reserve(sizeof(int2) * B));
   TRY(c->d_status.reserve(sizeof(int)));
-  TRY(c->d_Rt.reserve(sizeof(float) * rows * S * RS));
   // with argmin records: a rolling pair of fp32 layer tables per slot and one byte per cell of
   // every layer; without: the fp32 tables of all layers
   const bool lazy = (flags & GBMW_FLAG_LAZY_ARGMIN) != 0;
-  const bool runs = (flags & GBMW_FLAG_DENSE_ARITHMETIC) == 0 && gbmw::layer0_in_registers(S);
-  if (runs) TRY(c->d_sum.reserve(sizeof(float) * ((size_t)S * (EP / 64)) * (lazy ? rows : (size_t)2 * B)));
+  const bool runs = (flags & GBMW_FLAG_DENSE_ARITHMETIC) == 0 && search_takes_pruned(S, E, B);
+  TRY(c->d_Rt.reserve(sizeof(float) * rows * S * (runs ? S : RS)));
+  if (runs) TRY(c->d_row.reserve(sizeof(float4) * rows * S));
+  if (runs) TRY(c->d_sum.reserve(sizeof(float2) * ((size_t)S * (EP / 64)) * (lazy ? rows : (size_t)2 * B)));
   if (lazy) {
     TRY(c->d_C.reserve(sizeof(float) * slab * rows));
   } else {
@@ -639,17 +658,19 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
 
   gbmw::Tables& t = c->t;
   t.B = B; t.S = S; t.SP = SP; t.RS = RS; t.E = E; t.EP = EP; t.keep_all = lazy ? 1 : 0;
-  t.runs = runs ? 2 : 0;
-  t.Tsum = runs ? (float*)c->d_sum.p : nullptr;
+  t.runs = runs ? 1 : 0;
+  t.Tsum = runs ? (float2*)c->d_sum.p : nullptr;
   t.final_from = std::max(0, E - ob_max);              // Algorithm 3 reads best(e) from E - b_up on
-  t.L = (const int*)c->d_L.p; t.off = (const int*)c->d_off.p; t.perm = (const int*)c->d_perm.p;
-  t.c = gc; t.M = gM; t.Rt = (const float*)c->d_Rt.p;
+  t.L = (const int*)c->d_L.p; t.off = (const int*)c->d_off.p; t.perm = (const int2*)c->d_perm.p;
+  t.c = gc; t.M = gM;
+  t.Rt = runs ? nullptr : (const float*)c->d_Rt.p;
+  t.Rn = runs ? (const float*)c->d_Rt.p : nullptr;
+  t.Row = runs ? (const float4*)c->d_row.p : nullptr;
   t.Cbuf = (float*)c->d_C.p; t.A = lazy ? nullptr : (uint8_t*)c->d_A.p;
   t.Asum = (!lazy && runs) ? (uint8_t*)c->d_asum.p : nullptr;
   t.best = (float*)c->d_best.p; t.best_s = (uint8_t*)c->d_best_s.p;
   t.status = (int*)c->d_status.p;
   t.counts = nullptr;
-  t.prev_full = 0;
 
   HIP_TRY_B(hipEventCreate(&ev0));
   HIP_TRY_B(hipEventCreate(&ev1));
@@ -682,7 +703,8 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
   // every row of the slots is readable from the start (rows beyond a stage's layers are never used)
   for (auto [ptr, words] : {std::pair<void*, size_t>{gc, rows * d.S}, {gM, rows * d.S},
                             {s.Ob_g, split ? rows * d.S : 0}, {s.Oms_g, split ? rows * d.S : 0},
-                            {c->d_Rt.p, rows * d.S * (size_t)RS}})
+                            {c->d_Rt.p, rows * d.S * (size_t)(runs ? S : RS)},
+                            {c->d_row.p, runs ? 4 * rows * d.S : 0}})
     if (words) {
       hipLaunchKernelGGL(gbmw::k_fill_u32, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st,
                          (uint32_t*)ptr, words, 0u);
@@ -696,11 +718,11 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
   // per slot: layers it holds, first model layer, and which of its fp32 layer tables are in
   // memory (the rolling pair keeps the last two computed; hi = -1: none)
   std::vector<int> slotL(B, 0), slot_first(B, 0), c_hi(B, -1), c_lo(B, -1), mode(B, kSkip);
-  std::vector<char> last_full(B, 0);                 // the slot's newest table has every cell written
+  std::vector<int2> h_slots;
   std::vector<int> h_src, h_msrc, h_dst, h_touched, h_perm, h_flags(3 * (size_t)n);
   int rounds = 0, stage_solves = 0;
   long long cell_updates = 0;
-  const bool l0_in_regs = gbmw::layer0_in_registers(S);
+  const bool l0_in_regs = gbmw::layer0_in_registers(t);
 
   // One round: the slots with mode != kSkip get their new layer count slotL / first layer
   // slot_first, are brought up to date and read back into the pairs' stage results.
@@ -734,7 +756,6 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
         c_hi[b] = L - 1;
       } else {
         final_only.push_back(b);
-        last_full[b] = 0;                            // its newest table is now an older one
       }
     }
     const int nt = (int)h_touched.size();
@@ -760,7 +781,9 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
 
     const int nrows = (int)h_src.size();
     HIP_TRY(hipMemcpyAsync(c->d_L.p, slotL.data(), sizeof(int) * B, H2D, st));
-    HIP_TRY(hipMemcpyAsync(c->d_perm.p, h_perm.data(), sizeof(int) * h_perm.size(), H2D, st));
+    h_slots.clear();
+    for (int b : h_perm) h_slots.push_back(make_int2(b, off[b]));
+    HIP_TRY(hipMemcpyAsync(c->d_perm.p, h_slots.data(), sizeof(int2) * h_slots.size(), H2D, st));
     HIP_TRY(hipMemcpyAsync(g_first, slot_first.data(), sizeof(int) * B, H2D, st));
     HIP_TRY(hipMemcpyAsync(g_touched, h_touched.data(), sizeof(int) * nt, H2D, st));
     if (nrows) {
@@ -768,7 +791,8 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
       HIP_TRY(hipMemcpyAsync(g_msrc, h_msrc.data(), sizeof(int) * nrows, H2D, st));
       HIP_TRY(hipMemcpyAsync(g_dst, h_dst.data(), sizeof(int) * nrows, H2D, st));
       hipLaunchKernelGGL(gbmw::k_gather, dim3(nrows), dim3(256), 0, st, dc, dM, dR, g_src, g_msrc, g_dst, S,
-                         SP, RS, gc, gM, (float*)c->d_Rt.p, s.Ob, s.Oms, s.Ob_g, s.Oms_g);
+                         SP, RS, gc, gM, const_cast<float*>(t.Rt), const_cast<float*>(t.Rn),
+                         const_cast<float4*>(t.Row), s.Ob, s.Oms, s.Ob_g, s.Oms_g);
     }
     // layer 0 goes to memory where something reads it from there
     for (int g = 0; g < G; ++g) {
@@ -789,28 +813,17 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
         for (size_t x = 0; x < append.size();) {
           size_t y = x;
           while (y < append.size() && slotL[append[y]] == slotL[append[x]]) ++y;
-          // the kept table that the step extends: every cell written if all of these slots got
-          // theirs from a split launch
-          bool all_full = true;
-          for (size_t z = x; z < y; ++z) all_full = all_full && last_full[append[z]];
-          gbmw::launch_minplus(t, slotL[append[x]] - 1, a_first + (int)x, (int)(y - x), sg, all_full ? -1 : 0);
-          const bool now_full = gbmw::launch_is_split(t, (int)(y - x));
-          for (size_t z = x; z < y; ++z) last_full[append[z]] = now_full;
+          gbmw::launch_minplus(t, slotL[append[x]] - 1, a_first + (int)x, (int)(y - x), sg);
           x = y;
         }
         gbmw::launch_final(t, a_first, (int)h_perm.size() - a_first, sg);
       }
       const int gn = gfirst[g + 1] - gfirst[g];
       const int Lmax_g = gn ? slotL[h_perm[gfirst[g]]] : 0;
-      int n_prev = 0;                                      // a complete solve: layer l - 1 comes from the launch before
       for (int l = 1; l < Lmax_g; ++l) {
         int na = 0;
         while (na < gn && slotL[h_perm[gfirst[g] + na]] > l) ++na;
-        gbmw::launch_minplus(t, l, gfirst[g], na, sg, n_prev);
-        n_prev = na;
-        // the slots whose last layer this launch produced
-        for (int x = 0; x < na; ++x)
-          if (slotL[h_perm[gfirst[g] + x]] == l + 1) last_full[h_perm[gfirst[g] + x]] = gbmw::launch_is_split(t, na);
+        gbmw::launch_minplus(t, l, gfirst[g], na, sg);
       }
       gbmw::launch_final(t, gfirst[g], gn, sg);
       if (g > 0) {

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(64 * NW, (NW >= 8 && SP <= 44) ? 4 : 2) void k_laye
   __shared__ int go;
 
   const int slot = blockIdx.x / a.tiles, tile = blockIdx.x % a.tiles;
-  const int inst = t.perm[a.first + slot];
+  const int inst = t.perm[a.first + slot].x;
   const int S = t.S, E = t.E, EP = t.EP;
   const int Lb = t.L[inst], row0 = t.off[inst];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -564,3 +564,47 @@ def test_config5_all_modes_agree(g):
             for x, y, what in zip(ref, got, ("best", "best_s", "C", "A")):
                 assert np.array_equal(x.view(np.uint8), y.view(np.uint8)), (mode, what)
 
+
+
+@pytest.mark.parametrize("mode", ["records", "lazy-argmin"])
+@pytest.mark.parametrize("S", [3, 8, 16, 17, 24, 40, 64, 65, 130, 255])
+def test_pruned_step_where_plans_start_to_fit(g, S, mode):
+    """The layer step that looks only at the candidates that can still be minimal, where its bounds
+    are weakest: columns that become finite inside a group of 64 budgets, at its edges and beyond E,
+    memories shared by many strategies (up to S candidates in one group: more than a wave keeps),
+    transformation costs far above the layer costs (nothing can be left out) and all equal (ties),
+    forbidden strategies, a last group of a few budgets.  Every cell, record and plan against the
+    oracle; launches of 720 x 64 budgets (large) down to one instance (small).  Bit-exact: the bounds
+    only leave out sums that are strictly larger in fp32."""
+    E = 11 * 256 - 250 if S > 64 else 90 * 256 - 13
+    st = gi.Stream(6100 + S)
+    parts = []
+    for i in range(8):
+        L = 4 if i in (0, 1) else 3
+        c = st.integers(L * S, 1, 40).astype(np.float32).reshape(L, S)
+        R = st.integers(L * S * S, 0, 9).astype(np.float32).reshape(L, S, S)
+        step = (1, 7, 64, 97, 3, 1, 13, 500)[i]
+        M = (st.integers(L * S, 0, 6) * step + st.integers(1, 0, 90)[0]).reshape(L, S)
+        if i == 1:
+            R *= 1000.0                              # nothing can be left out
+        if i == 2:
+            R[:] = 1.0                               # ties everywhere
+            c[:] = 2.0
+        if i == 3:
+            c[0, ::2] = np.inf
+            R[1, :, 1::3] = np.inf
+        if i == 4:
+            M[0] = E - st.integers(S, 0, 130)        # finite only in the last groups
+            M[1:] = 0
+        if i == 5:
+            M[0] = E + 1                             # nothing fits
+        parts.append(gi.Problem(1, S, E, np.array([L]), c, M, R))
+    p = gi.stack(parts, f"pruned-S{S}")
+    lazy = mode == "lazy-argmin"
+    ctx = solve_gpu(p, flags=(g.GBMW_FLAG_LAZY_ARGMIN if lazy else g.GBMW_FLAG_KEEP_ALL_C) | g.GBMW_FLAG_ONE_STREAM,
+                    device_inputs=True)
+    best, best_s = g.gbmw_get_best(ctx)
+    for b in range(p.B):
+        _log(f"pruned S={S} {mode} instance {b}")
+        check_instance(g, ctx, p, b, full_C=True, q_es=[0, 63, 64, 700, E - 1, E], best=best, best_s=best_s)
+    g.gbmw_destroy(ctx)
