@@ -875,15 +875,17 @@ void launch_backtrack(const Tables& t, int nq, const int* q_inst, const int* q_e
 // of all O_f and suf_i the sum over the layers above i, so
 //   E_all = F + max_i (O_b(i) - suf_i) + sum O_ms.
 // ---------------------------------------------------------------------------
+// WAVE: all lanes of the wave walk the same plan and lane 0 writes it.
+template <bool WAVE>
 __device__ long long walk_plan(const Tables& t, int inst, int e, const int* __restrict__ Of,
                                const int* __restrict__ Ob, const int* __restrict__ Oms,
-                               uint8_t* plan) {
+                               uint8_t* plan, int lane) {
   const int Lb = t.L[inst], row0 = t.off[inst], S = t.S;
   int s = t.best_s[(size_t)inst * t.EP + e];
   long long suf = 0, ms = 0, mx = 0;
   for (int l = Lb - 1; l >= 0; --l) {
     const size_t cell = (size_t)(row0 + l) * S + s;
-    if (plan) plan[l] = (uint8_t)s;
+    if (plan && (!WAVE || lane == 0)) plan[l] = (uint8_t)s;
     const long long here = (long long)Ob[cell] - suf;
     mx = (l == Lb - 1 || here > mx) ? here : mx;
     suf += Of[cell];
@@ -892,7 +894,7 @@ __device__ long long walk_plan(const Tables& t, int inst, int e, const int* __re
       const int m = t.M[cell];
       e -= m;                                            // budget left for layers < l
       if (m < 0 || e < 0) return -2;                     // only reachable with invalid inputs
-      s = pred_strategy(t, row0 + l, s, e);
+      s = WAVE ? pred_strategy_wave(t, row0 + l, s, e, lane) : pred_strategy(t, row0 + l, s, e);
     }
   }
   return suf + mx + ms;
@@ -914,12 +916,18 @@ __global__ __launch_bounds__(64) void k_select_check(Tables t, const int* __rest
   const int base = t.E - bup[inst];                      // last budget that needs no check
   const int lo = (base < 0 ? -1 : base) + 1;
   const int e = lo + blockIdx.x * 64 + threadIdx.x;
+  // budgets above a failure already recorded have nothing to add
+  if (*(volatile const int*)&first_bad[inst] < lo + (int)blockIdx.x * 64) return;
   if (e > t.E) return;
   if (t.best[(size_t)inst * t.EP + e] == INFINITY) return;   // no plan: nothing to check
-  const long long ea = walk_plan(t, inst, e, Of, Ob, Oms, nullptr);
+  const long long ea = walk_plan<false>(t, inst, e, Of, Ob, Oms, nullptr, 0);
   if (ea > (long long)t.E || ea < 0) atomicMin(&first_bad[inst], e);
 }
 
+// One wave per instance: all lanes walk the chosen plan together and, without records, share the
+// recomputation of each step (pred_strategy_wave); lane 0 writes.  One lane per instance took
+// 0.78 ms for 64 instances of up to 24 layers and 44 strategies without records (latency: every step
+// is S dependent candidates), a wave takes 0.06 ms.
 __global__ __launch_bounds__(64) void k_select_pick(Tables t, const int* __restrict__ Of,
                                                     const int* __restrict__ Ob,
                                                     const int* __restrict__ Oms,
@@ -929,8 +937,7 @@ __global__ __launch_bounds__(64) void k_select_pick(Tables t, const int* __restr
                                                     float* __restrict__ cost,
                                                     uint8_t* __restrict__ plan,
                                                     int* __restrict__ e_all) {
-  const int inst = blockIdx.x * 64 + threadIdx.x;
-  if (inst >= t.B) return;
+  const int inst = blockIdx.x, lane = threadIdx.x;
   const int base = t.E - bup[inst];
   const int init = base < 0 ? -1 : base;
   const int fb = first_bad[inst];
@@ -938,16 +945,17 @@ __global__ __launch_bounds__(64) void k_select_pick(Tables t, const int* __restr
   int opt = init;
   if (last > init && t.best[(size_t)inst * t.EP + last] != INFINITY) opt = last;
   uint8_t* p = plan + (size_t)inst * Lmax;
-  for (int l = 0; l < Lmax; ++l) p[l] = 0xFF;
-  e_opt[inst] = opt;
   float cst = INFINITY;
   long long ea = -1;
-  if (opt >= 0) {
-    cst = t.best[(size_t)inst * t.EP + opt];
-    if (cst != INFINITY) ea = walk_plan(t, inst, opt, Of, Ob, Oms, p);
+  if (opt >= 0) cst = t.best[(size_t)inst * t.EP + opt];
+  const bool any = cst != INFINITY;
+  for (int l = (any ? t.L[inst] : 0) + lane; l < Lmax; l += 64) p[l] = 0xFF;
+  if (any) ea = walk_plan<true>(t, inst, opt, Of, Ob, Oms, p, lane);
+  if (lane == 0) {
+    e_opt[inst] = opt;
+    cost[inst] = cst;
+    e_all[inst] = (int)ea;
   }
-  cost[inst] = cst;
-  e_all[inst] = (int)ea;
 }
 
 void launch_select(const Tables& t, const int* Of, const int* Ob, const int* Oms, const int* bup,
@@ -957,7 +965,7 @@ void launch_select(const Tables& t, const int* Of, const int* Ob, const int* Oms
   if (max_window > 0)
     hipLaunchKernelGGL(k_select_check, dim3((max_window + 63) / 64, t.B), dim3(64), 0, st, t, Of,
                        Ob, Oms, bup, first_bad);
-  hipLaunchKernelGGL(k_select_pick, dim3((t.B + 63) / 64), dim3(64), 0, st, t, Of, Ob, Oms, bup,
+  hipLaunchKernelGGL(k_select_pick, dim3(t.B), dim3(64), 0, st, t, Of, Ob, Oms, bup,
                      first_bad, Lmax, e_opt, cost, plan, e_all);
 }
 
