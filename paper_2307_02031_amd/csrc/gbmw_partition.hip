@@ -440,8 +440,8 @@ size_t carve_search(Carver& cv, const Dims& d, bool with_cns, bool with_split, g
   s.stCns = cv.take<float>(d.sumP);
   s.stO = cv.take<int>(d.sumP);
   s.strat = cv.take<uint8_t>(d.sumLm);
-  s.moved = cv.take<int>(2 * d.n);
-  s.live = cv.take<int>(d.n);
+  s.live = cv.take<int>(3 * d.n);                        // and moved: read back together every round
+  s.moved = s.live ? s.live + d.n : nullptr;
   s.bup = with_split ? cv.take<int>(d.sumP) : nullptr;
   s.first_bad = with_split ? cv.take<int>(d.sumP) : nullptr;
   // everything from here on starts as zero
@@ -608,20 +608,15 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
   // rows of the slots (what the layer kernels read) and the per-round index arrays
   const size_t rows = (size_t)rows_total;
   float* gc = nullptr;
-  int *gM = nullptr, *g_src = nullptr, *g_msrc = nullptr, *g_dst = nullptr, *g_touched = nullptr,
-      *g_chain = nullptr, *g_first = nullptr, *g_group = nullptr;
+  int *gM = nullptr, *g_round = nullptr, *g_chain = nullptr, *g_group = nullptr;
   float *g_batch = nullptr, *g_tpt = nullptr;
   auto carve_gather = [&](Carver& w) {
     gc = w.take<float>(rows * d.S);
     gM = w.take<int>(rows * d.S);
     s.Ob_g = split ? w.take<int>(rows * d.S) : nullptr;
     s.Oms_g = split ? w.take<int>(rows * d.S) : nullptr;
-    g_src = w.take<int>(rows);
-    g_msrc = w.take<int>(rows);
-    g_dst = w.take<int>(rows);
-    g_touched = w.take<int>(d.sumP);
+    g_round = w.take<int>(5 * d.sumP + 3 * rows);
     g_chain = w.take<int>(d.sumP);
-    g_first = w.take<int>(d.sumP);
     g_group = w.take<int>(d.n);
     g_batch = w.take<float>(d.n);
     g_tpt = w.take<float>(4);
@@ -633,10 +628,13 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
     Carver cv(c->d_gather.p);
     carve_gather(cv);
   }
-  TRY(c->d_L.reserve(sizeof(int) * B));
   TRY(c->d_off.reserve(sizeof(int) * B));
-  TRY(c->d_perm.reserve(sizeof(int2) * B));
   TRY(c->d_status.reserve(sizeof(int)));
+  // Everything a round sends goes in one copy (seven small ones took 60 us of every round, host and
+  // device): per slot its layers, its first model layer, (slot, first row) in launch order and the
+  // touched slots, then per row to gather its source, its memory's source and its place.
+  int2* g_slots = (int2*)g_round;
+  int *g_L = g_round + 2 * B, *g_first = g_L + B, *g_touched = g_first + B, *g_rows = g_touched + B;
   // with argmin records: a rolling pair of fp32 layer tables per slot and one byte per cell of
   // every layer; without: the fp32 tables of all layers
   const bool lazy = (flags & GBMW_FLAG_LAZY_ARGMIN) != 0;
@@ -661,7 +659,7 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
   t.runs = runs ? 1 : 0;
   t.Tsum = runs ? (float2*)c->d_sum.p : nullptr;
   t.final_from = std::max(0, E - ob_max);              // Algorithm 3 reads best(e) from E - b_up on
-  t.L = (const int*)c->d_L.p; t.off = (const int*)c->d_off.p; t.perm = (const int2*)c->d_perm.p;
+  t.L = g_L; t.off = (const int*)c->d_off.p; t.perm = g_slots;
   t.c = gc; t.M = gM;
   t.Rt = runs ? nullptr : (const float*)c->d_Rt.p;
   t.Rn = runs ? (const float*)c->d_Rt.p : nullptr;
@@ -718,8 +716,7 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
   // per slot: layers it holds, first model layer, and which of its fp32 layer tables are in
   // memory (the rolling pair keeps the last two computed; hi = -1: none)
   std::vector<int> slotL(B, 0), slot_first(B, 0), c_hi(B, -1), c_lo(B, -1), mode(B, kSkip);
-  std::vector<int2> h_slots;
-  std::vector<int> h_src, h_msrc, h_dst, h_touched, h_perm, h_flags(3 * (size_t)n);
+  std::vector<int> h_round, h_src, h_msrc, h_dst, h_touched, h_perm, h_flags(3 * (size_t)n);
   int rounds = 0, stage_solves = 0;
   long long cell_updates = 0;
   const bool l0_in_regs = gbmw::layer0_in_registers(t);
@@ -780,16 +777,18 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
     h_perm.insert(h_perm.end(), final_only.begin(), final_only.end());
 
     const int nrows = (int)h_src.size();
-    HIP_TRY(hipMemcpyAsync(c->d_L.p, slotL.data(), sizeof(int) * B, H2D, st));
-    h_slots.clear();
-    for (int b : h_perm) h_slots.push_back(make_int2(b, off[b]));
-    HIP_TRY(hipMemcpyAsync(c->d_perm.p, h_slots.data(), sizeof(int2) * h_slots.size(), H2D, st));
-    HIP_TRY(hipMemcpyAsync(g_first, slot_first.data(), sizeof(int) * B, H2D, st));
-    HIP_TRY(hipMemcpyAsync(g_touched, h_touched.data(), sizeof(int) * nt, H2D, st));
+    h_round.assign(5 * (size_t)B, 0);
+    for (size_t x = 0; x < h_perm.size(); ++x) {
+      h_round[2 * x] = h_perm[x];
+      h_round[2 * x + 1] = off[h_perm[x]];
+    }
+    std::copy(slotL.begin(), slotL.end(), h_round.begin() + 2 * B);
+    std::copy(slot_first.begin(), slot_first.end(), h_round.begin() + 3 * B);
+    std::copy(h_touched.begin(), h_touched.end(), h_round.begin() + 4 * B);
+    for (const std::vector<int>* v : {&h_src, &h_msrc, &h_dst}) h_round.insert(h_round.end(), v->begin(), v->end());
+    HIP_TRY(hipMemcpyAsync(g_round, h_round.data(), sizeof(int) * h_round.size(), H2D, st));
     if (nrows) {
-      HIP_TRY(hipMemcpyAsync(g_src, h_src.data(), sizeof(int) * nrows, H2D, st));
-      HIP_TRY(hipMemcpyAsync(g_msrc, h_msrc.data(), sizeof(int) * nrows, H2D, st));
-      HIP_TRY(hipMemcpyAsync(g_dst, h_dst.data(), sizeof(int) * nrows, H2D, st));
+      const int *g_src = g_rows, *g_msrc = g_rows + nrows, *g_dst = g_msrc + nrows;
       hipLaunchKernelGGL(gbmw::k_gather, dim3(nrows), dim3(256), 0, st, dc, dM, dR, g_src, g_msrc, g_dst, S,
                          SP, RS, gc, gM, const_cast<float*>(t.Rt), const_cast<float*>(t.Rn),
                          const_cast<float4*>(t.Row), s.Ob, s.Oms, s.Ob_g, s.Oms_g);
@@ -843,8 +842,7 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
     hipLaunchKernelGGL(gbmw::k_chain_step, dim3(n), dim3(64), 0, st, s, phase);
     HIP_TRY(hipGetLastError());
     // accept flags: live | moved (two per pair); the wait also ends the round for the host vectors
-    HIP_TRY(hipMemcpyAsync(h_flags.data(), s.live, sizeof(int) * n, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(h_flags.data() + n, s.moved, sizeof(int) * 2 * n, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(h_flags.data(), s.live, sizeof(int) * 3 * n, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     return GBMW_OK;
   };
