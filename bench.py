@@ -87,7 +87,7 @@ def kernel_roofline(g, torch, p, d, args, flags, step_sec):
     """The dominant kernel (k_minplus: Eq. 3's inner minimum fused with the shift-add), one launch per
     layer: average duration from HIP event pairs around every launch on the solve's stream (one stream),
     and the work the launches really did from the library's path counters (a second, untimed solve
-    with GBMW_FLAG_COUNT_WORK: which waves took the run shortcut depends on the inputs alone).
+    with GBMW_FLAG_COUNT_WORK: which groups read one column depends on the inputs alone).
 
     achieved = executed lane-ops per launch / average launch duration, with 2 lane-ops (one add, one
     min) per candidate update that a lane or a run really computed; covered / executed updates is
@@ -118,25 +118,18 @@ def kernel_roofline(g, torch, p, d, args, flags, step_sec):
     upd_dense = tot[3] * 64 * S                                            # a row: 64 lanes x S' candidates
     upd_exec = upd_runs + upd_dense
     covered = p.executed_updates()
-    # HBM bytes by path (the R tile of an instance's layer, S x (S'+2) floats padded to quads, comes from
-    # HBM once per XCD, whose L2 then serves the workgroups):
-    #   dense row (wave, s): 64 x 4 B of the previous table read (not in the layer-1 launch), 64 x 4 B of
-    #     the new table and 64 x 1 B of records written, one summary word
-    #     (with the run shortcut also the byte that says the group's records are in A)
-    #   run wave: per strategy M and two summary words read (12 B), one summary word and one record byte
-    #     for the group written; if it was recognised only from the loaded values it has read its 64 x 4 B
-    #     per strategy too
-    #   run workgroup (4 waves): 4 x the reads, four summary words and four record bytes per strategy
+    # HBM bytes with dense arithmetic: per row (wave, s) 64 x 4 B of the previous table read (not in the
+    # layer-1 launch), 64 x 4 B of the new table and 64 x 1 B of records written; the R tile of an instance's
+    # layer, S x (S'+2) floats padded to quads, comes from HBM once per XCD, whose L2 then serves the workgroups
     rec = 1 if records else 0
-    sumw = 0 if dense else 4
-    grp = rec if not dense else 0
     read_b = write_b = 0
     RS = (S + 3) // 4 * 4 + 4                                              # a row of the R tile in floats
     for i, w in enumerate(work):
-        read_b += int((p.L > i + 1).sum()) * 8 * S * RS * 4                # launch i is layer i + 1 (one stream)
-        read_b += w[3] * (256 if i > 0 else 0) + (w[1] + w[2] + 4 * w[0]) * 12 * S + (w[2] * 256 * S if i > 0 else 0)
-        write_b += w[3] * (256 + 64 * rec + sumw + grp) + (w[1] + w[2]) * S * (rec + 4) + w[0] * S * (4 * rec + 16)
+        read_b += int((p.L > i + 1).sum()) * 8 * S * RS * 4 + w[3] * (256 if i > 0 else 0)   # launch i is layer i + 1
+        write_b += w[3] * (256 + 64 * rec)
     avg_launch_s = mp_ms / mp_n * 1e-3 if mp_n else float("nan")
+    # the default mode computes only the candidates that can still be minimal, which is not counted: the
+    # figures from the counters are exact with dense arithmetic and upper bounds (null here) without it
     ach = OPS_PER_UPDATE * upd_exec / n_launch / avg_launch_s / 1e12 if mp_n else 0.0
     hbm_model = (read_b + write_b) / n_launch if n_launch else 0.0
     traffic, traffic_source = None, None
@@ -153,25 +146,27 @@ def kernel_roofline(g, torch, p, d, args, flags, step_sec):
                                   f"in this run")
     return {
         "kernel": "k_minplus (fused min-plus + argmin + shift-add), one launch per layer",
-        "mode": "dense arithmetic" if dense else "run shortcut (default)",
-        "bound": "alu", "achieved": ach, "peak": PEAK_PLAIN_FP32_TOPS, "unit": "TFLOP/s",
-        "frac": ach / PEAK_PLAIN_FP32_TOPS,
+        "mode": "dense arithmetic" if dense else "pruned layer step (default)",
+        "bound": "alu" if dense else "latency", "achieved": ach if dense else None, "peak": PEAK_PLAIN_FP32_TOPS, "unit": "TFLOP/s",
+        "frac": ach / PEAK_PLAIN_FP32_TOPS if dense else None,
         "peak_is": "plain (non-packed, non-FMA) fp32 VALU lane-ops: 256 CU x 64 lanes x 2.4 GHz = 39.3 T/s; "
                    "the published 157.3 TFLOP/s is this x2 packed x2 FMA",
-        "frac_of_published_fp32_vector_peak": ach / PEAK_PUBLISHED_FP32_TFLOPS,
+        "frac_of_published_fp32_vector_peak": ach / PEAK_PUBLISHED_FP32_TFLOPS if dense else None,
         "ops_per_update": OPS_PER_UPDATE,
         "valu_instr_floor_per_update": 1.5,
-        "frac_of_instr_floor": ach / OPS_PER_UPDATE * 1.5 / PEAK_PLAIN_FP32_TOPS,
+        "frac_of_instr_floor": ach / OPS_PER_UPDATE * 1.5 / PEAK_PLAIN_FP32_TOPS if dense else None,
         "note": "achieved = 2 lane-ops (add, min) x candidate updates really computed per launch / average "
                 "launch duration; a three-input min folds two candidates, so the instruction floor is 1.5 per "
                 "update and frac_of_instr_floor is the share of the VALU issue rate that floor would need",
-        "executed_updates_per_launch": upd_exec / n_launch if n_launch else 0,
+        "executed_updates_per_launch": upd_exec / n_launch if n_launch and dense else None,
+        "executed_updates_per_launch_at_most": upd_exec / n_launch if n_launch else 0,
         "covered_updates_per_launch": covered / n_launch if n_launch else 0,
-        "shortcut_gain": covered / upd_exec if upd_exec else None,
+        "shortcut_gain_at_least": covered / upd_exec if upd_exec else None,
         "work_per_solve": {"run_workgroups": tot[0], "run_waves_by_summary": tot[1], "run_waves_by_value": tot[2],
                            "dense_rows": tot[3]},
-        "hbm": {"modelled_bytes_per_launch": hbm_model, "achieved_GBps": hbm_model / avg_launch_s / 1e9 if mp_n else 0.0,
-                "peak": 8000.0, "frac": hbm_model / avg_launch_s / 8e12 if mp_n else 0.0,
+        "hbm": {"modelled_bytes_per_launch": hbm_model if dense else None,
+                "achieved_GBps": hbm_model / avg_launch_s / 1e9 if mp_n and dense else None,
+                "peak": 8000.0, "frac": hbm_model / avg_launch_s / 8e12 if mp_n and dense else None,
                 "dense_formulation_bytes_per_launch": (8.0 + rec) * covered / S / n_launch if n_launch else 0.0},
         "traffic": traffic, "traffic_source": traffic_source,
         "avg_launch_ms": avg_launch_s * 1e3, "launches_per_solve": n_launch,
@@ -351,7 +346,7 @@ def main():
         "roofline": roofline,
     }
     # The same solve with every lane computing its own cell (GBMW_FLAG_DENSE_ARITHMETIC): what the
-    # arithmetic itself reaches against the ALU roofline, without the shortcut for runs of equal columns.
+    # arithmetic itself reaches against the ALU roofline, without leaving candidates out.
     if not args.dense_arithmetic:
         dflags = base_flags | g.GBMW_FLAG_DENSE_ARITHMETIC
         dctx, dsec = solve_steps(g, torch, p, d, args.steps, args.warmup, flags=dflags)
@@ -362,7 +357,7 @@ def main():
         out["roofline"]["frac_with_every_update_executed"] = dr["frac"]
         out["roofline"]["frac_with_every_update_executed_is"] = (
             "roofline.frac of the same solve under GBMW_FLAG_DENSE_ARITHMETIC (object dense_arithmetic): the default "
-            "mode's run shortcut executes one update in shortcut_gain, so its launches are short and bound by "
+            "mode leaves out the candidates that cannot be minimal, so its launches are short and bound by "
             "neither roofline")
     # The same solve without argmin records (GBMW_FLAG_LAZY_ARGMIN): every layer's fp32 table
     # is kept and the walkers recompute the records they need.  Reported beside the headline,

@@ -3,7 +3,7 @@
 //
 // Device data layout ("SoA by strategy", budget axis contiguous):
 //   C table of one (instance, layer):  float  [S][EP]   C[s*EP + e]
-//   A table of one (instance, layer):  uint8  [S][EP]   A[s*EP + e']   (with the run shortcut one byte
+//   A table of one (instance, layer):  uint8  [S][EP]   A[s*EP + e']   (with the pruned step one byte
 //       per group of 64 budgets stands for the group's 64 records where they are equal: Tables::Asum)
 //   EP = (E + 1) rounded up to a multiple of 256 (row stride in elements)
 //   Rt: transposed, padded transformation cost with the layer's own cost and

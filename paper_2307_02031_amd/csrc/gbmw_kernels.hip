@@ -509,7 +509,7 @@ struct Blocking {                       // budgets per lane for a given strategy
   // without the argmin pass: the SP table values plus about 16 working registers
   static constexpr int MINW_VALUES = (SP <= 44) ? 8 : (SP <= 52) ? 7 : (SP <= 60) ? 6 : (SP <= 64) ? 5 : (SP <= 96) ? 4 : 3;
   // the pruned step: up to 32 KB of LDS per workgroup leave five workgroups per compute unit
-  // (at four waves per SIMD beside it the layer-1 variant would spill two registers less than none)
+  // (the layer-1 variant needs a few registers more: at five waves per SIMD it spills two)
   static constexpr int MINW_RUNS = 5, MINW_RUNS_FIRST = 4;
 };
 

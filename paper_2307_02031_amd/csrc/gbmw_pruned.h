@@ -1,5 +1,5 @@
-// Device code of the layer step that looks only at what can still be minimal (the run shortcut:
-// Tables::runs != 0).  Internal; included by gbmw_kernels.hip.
+// Device code of the layer step that looks only at what can still be minimal
+// (Tables::runs != 0).  Internal; included by gbmw_kernels.hip.
 //
 // Along the budget axis every table is a non-increasing step function, and every layer leaves,
 // per strategy and group of 64 budgets e' of its min-plus product, the value T + c at the
@@ -21,6 +21,14 @@
 //     (mostly one: then a row is two additions and a store);
 //   - more than kept() candidates (the groups where the first plans start to fit, where there is
 //     no upper bound yet): the four waves of the workgroup share the group (big_group).
+//
+// What bounds it: the chain of one group (2 to 5 us of loads, 1 to 4 us of bounds, 5 to 18 us of cells)
+// and the fetch of its 40 to 90 KB of code, neither bytes (46 MB per launch at B=64, S=44, E=32768:
+// 1.1 TB/s) nor arithmetic.  Fills, before (all candidates unless a wave's columns are constant; no
+// such shortcut beyond 64 strategies) -> with this step: B=64 S=44 E=32768 1.08 -> 0.80 ms, B=16
+// L=96 S=64 E=65536 14.6 -> 7.2 ms, B=16 S=128 E=32768 4.8 -> 0.73 ms.  Everything unrolled over
+// candidates is therefore sized to them (8 or kept()) and called from one place: at 84 to 215 KB of
+// code the same step spilled scalar registers and took 30 to 40 % longer.
 #pragma once
 #include "gbmw_kernels.h"
 
