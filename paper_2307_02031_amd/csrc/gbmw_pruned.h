@@ -343,6 +343,14 @@ __device__ __forceinline__ int store_records(uint8_t* __restrict__ An, int EP, i
   return kNoGroupRecord;
 }
 
+// Output s of a group in which no predecessor fits: +inf throughout, record 0.
+template <bool ARG>
+__device__ __forceinline__ void no_predecessor(const Tables& t, int inst, int row, int l, int wb, int s) {
+  const size_t at = (size_t)s * (t.EP >> 6) + (wb >> 6);
+  sum_table(t, inst, row, l)[at] = make_float2(INFINITY, INFINITY);
+  if (ARG) group_records(t, row)[at] = 0;
+}
+
 // Cells, summaries and records of one group for the outputs s = sfirst + lane (valid lanes), given
 // the columns of its K <= KEEP candidates in LDS: lane k holds candidate k's strategy (listv, in
 // index order) and the place of its column (slotv).  estar: first budget of the group at which a
@@ -671,8 +679,9 @@ __device__ __forceinline__ bool dense_group(const Tables& t, int inst, int row, 
             bool live = false;
 #pragma unroll
             for (int oc = 0; oc < NCH; ++oc) {
-              if (pass == 0) tub[oc] = __builtin_fminf(tub[oc], lane_f(ub[c], k[i]) + r[i][oc]);
-              else live = live || (64 * oc + lane < S && lane_f(lb[c], k[i]) + r[i][oc] <= tub[oc]);
+              const float x = lane_f(pass == 0 ? ub[c] : lb[c], k[i]) + r[i][oc];
+              if (pass == 0) tub[oc] = __builtin_fminf(tub[oc], x);
+              else live = live || (64 * oc + lane < S && x <= tub[oc]);
             }
             if (pass == 1 && __builtin_amdgcn_ballot_w64(live) != 0) keep |= 1ull << k[i];
           }
@@ -788,7 +797,10 @@ __device__ __forceinline__ void big_group(const Tables& t, int inst, int row, in
   const int per = (S + kWaves - 1) / kWaves;             // at most 64
   const int sfirst = wave * per;
   const bool valid = lane < per && sfirst + lane < S;
-  if (K2 <= KEEP) {
+  if (K2 == 0) {
+    // a column's words may speak for budgets beyond this group: no column is finite inside it after all
+    if (valid) no_predecessor<ARG>(t, inst, row, l, wb, sfirst + lane);
+  } else if (K2 <= KEEP) {
     const int v = (int)list[lane < K2 ? lane : K2 - 1];
     rows<KEEP, STAGED, ARG>(t, inst, row, l, wb, n_in, lane, K2, v & 255, v >> 8, estar, col, rt, sfirst, valid);
   } else {

@@ -608,3 +608,29 @@ def test_pruned_step_where_plans_start_to_fit(g, S, mode):
         _log(f"pruned S={S} {mode} instance {b}")
         check_instance(g, ctx, p, b, full_C=True, q_es=[0, 63, 64, 700, E - 1, E], best=best, best_s=best_s)
     g.gbmw_destroy(ctx)
+
+
+@pytest.mark.parametrize("mode", ["records", "lazy-argmin"])
+@pytest.mark.parametrize("copies", [230, 350, 500], ids=["shared-groups", "one-group-waves", "four-group-waves"])
+@pytest.mark.parametrize("S", [17, 40, 64, 70, 130, 255])
+def test_groups_that_no_plan_reaches_yet(g, S, copies, mode):
+    """Columns whose words speak for budgets beyond the group that reads them: all S of them look like
+    candidates (more than a wave keeps) although none is finite up to the group's end; a last group
+    whole and cut by E.  Three instances, copied until the launches have each of their shapes (a
+    group per workgroup, one and four groups per wave); every cell, record and plan of each."""
+    parts = []
+    E = 255 if copies < 350 else 700
+    for i, (first, then) in enumerate([(70, 60), (40, 30), (E - 59, 40)]):
+        p = gi.random_instance(7000 + S + i, 3, S, E, M_rng=(1, 9), R_rng=(0.0, 4.0))
+        p.M[0], p.M[1] = first, then
+        parts.append(p)
+    p = gi.stack(parts * copies, f"unreached-S{S}")
+    _log(f"unreached S={S} copies={copies} {mode}")
+    ctx = solve_gpu(p, flags=(g.GBMW_FLAG_LAZY_ARGMIN if mode != "records" else g.GBMW_FLAG_KEEP_ALL_C)
+                    | g.GBMW_FLAG_ONE_STREAM, device_inputs=True)
+    best, best_s = g.gbmw_get_best(ctx)
+    for b in range(3):
+        check_instance(g, ctx, p, b, full_C=True, q_es=list(range(0, E + 1, 7)) + [E], best=best, best_s=best_s)
+        for copy in range(b, p.B, 3):
+            assert np.array_equal(best[copy].view(np.uint32), best[b].view(np.uint32)) and np.array_equal(best_s[copy], best_s[b])
+    g.gbmw_destroy(ctx)

@@ -1,0 +1,66 @@
+"""The layer step over the candidates that can still be minimal (csrc/gbmw_pruned.h) on the CPU: its
+source compiled for the host, a fiber per lane (tests/host_wave), under AddressSanitizer, against
+the oracle bit for bit.  No GPU: an access out of range ends a child process here, not a device."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import gbmw_inputs as gi
+import oracle
+import pins
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2307_02031_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    exe = tmp_path_factory.mktemp("host_wave") / "pruned"
+    src = os.path.join(HERE, "host_wave")
+    # no stack instrumentation: the fibers' stacks are not the sanitizer's
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-w", "-ffp-contract=off", "-fsanitize=address",
+                    "--param", "asan-stack=0", "-D__HIPCC__", "-I", src, "-I", CSRC, os.path.join(src, "pruned.cpp"),
+                    "-o", str(exe)], check=True)
+    return exe
+
+
+def run(program, tmp_path, p, unit, records):
+    """Tables and records of one instance; unit: groups of 64 budgets per wave (0: four waves share one)."""
+    L, S, E = int(p.L[0]), p.S, p.E
+    src, dst = tmp_path / "in", tmp_path / "out"
+    with open(src, "wb") as f:
+        np.array([S, E, L, unit, records], np.int32).tofile(f)
+        for a, t in ((p.c, np.float32), (p.M, np.int32), (p.R, np.float32)):
+            np.ascontiguousarray(a, t).tofile(f)
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1")
+    r = subprocess.run([str(program), str(src), str(dst)], env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[:3000]
+    with open(dst, "rb") as f:
+        C = np.fromfile(f, np.float32, L * (E + 1) * S).reshape(L, E + 1, S)
+        A = np.fromfile(f, np.uint8, L * (E + 1) * S).reshape(L, E + 1, S)
+    return C, A
+
+
+def check(program, tmp_path, p, unit, records):
+    C, A = run(program, tmp_path, p, unit, records)
+    ref = oracle.solve_problem(p, 0, keep_C=True, keep_A=True, nthreads=4)
+    for l in range(int(p.L[0])):
+        pins.assert_same_f32(C[l], ref.C[l], f"{p.name} unit {unit} records {records} C layer {l}")
+        assert np.array_equal(A[l], ref.A[l]), f"{p.name} unit {unit} records {records} A layer {l}"
+
+
+SHAPES = [(0, 1), (0, 0), (1, 1), (4, 0), (4, 1)]         # (groups per wave, records)
+
+
+@pytest.mark.parametrize("S", [17, 40, 64, 70, 130, 255])
+def test_a_group_that_no_plan_reaches_yet(program, tmp_path, S):
+    """The two words of a column speak for 64 budgets of their own, which may end beyond the group that
+    reads them: every column can look like a candidate although none is finite up to the group's end.
+    More of them than a wave keeps go to the whole workgroup, whose second look then leaves none."""
+    for first, then, E in ((70, 60, 300), (40, 30, 200), (70, 60, 127), (40, 30, 100)):   # the last group whole / cut by E
+        p = gi.random_instance(7000 + S, 4, S, E, M_rng=(1, 9), R_rng=(0.0, 4.0))
+        p.M[0], p.M[1] = first, then
+        for unit, records in SHAPES[:4]:
+            check(program, tmp_path, p, unit, records)
