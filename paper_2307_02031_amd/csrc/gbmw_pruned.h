@@ -692,6 +692,13 @@ __device__ __forceinline__ bool dense_group(const Tables& t, int inst, int row, 
 #pragma unroll
     for (int c = 0; c < NCH; ++c) K += __builtin_popcountll(cand[c]);
     if (K > KEEP) return false;
+    if (K == 0) {
+      // only with entries of R that no comparison holds for (NaN: the solve is refused once it has run)
+#pragma unroll
+      for (int oc = 0; oc < NCH; ++oc)
+        if (part == 0 && 64 * oc + lane < S) no_predecessor<ARG>(t, inst, row, l, wb, 64 * oc + lane);
+      return true;
+    }
   }
 
   // sized to the candidates: the unrolled loops run for all of their slots

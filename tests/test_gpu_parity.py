@@ -634,3 +634,29 @@ def test_groups_that_no_plan_reaches_yet(g, S, copies, mode):
         for copy in range(b, p.B, 3):
             assert np.array_equal(best[copy].view(np.uint32), best[b].view(np.uint32)) and np.array_equal(best_s[copy], best_s[b])
     g.gbmw_destroy(ctx)
+
+
+@pytest.mark.parametrize("S", [40, 70, 130])
+def test_a_slab_of_nan_is_refused_and_nothing_else_happens(g, S):
+    """Device inputs whose R is NaN for a whole layer in which more columns start to fit than a wave
+    keeps: no bound holds for any of them.  The solve ends, every waiting call refuses it, and the
+    context then solves the same sizes with sound values."""
+    import torch
+    parts = []
+    for i in range(3):
+        p = gi.random_instance(7300 + S + i, 4, S, 600, M_rng=(0, 3), R_rng=(0.0, 4.0))
+        p.M[0] = 70
+        parts.append(p)
+    p = gi.stack(parts * 150, f"nan-S{S}")
+    c, M, R = (torch.from_numpy(x).cuda() for x in (p.c, p.M, p.R))
+    R[2::4] = float("nan")
+    for flags in (0, g.GBMW_FLAG_LAZY_ARGMIN):
+        ctx = g.gbmw_dp_solve_batched(p.L, c, M, R, S, p.E, flags=flags)
+        for call in (g.gbmw_synchronize, g.gbmw_get_best, lambda c: g.gbmw_backtrack(c, [0], [p.E])):
+            with pytest.raises(g.GbmwError) as ei:
+                call(ctx)
+            assert ei.value.status == g.GBMW_ERR_INVALID_ARG and "R" in str(ei.value)
+        ctx = solve_gpu(p, flags=flags, device_inputs=True, ctx=ctx)
+        for b in range(3):
+            check_instance(g, ctx, p, b, full_C=False, q_es=[0, 70, 71, 127, 300, p.E])
+        g.gbmw_destroy(ctx)

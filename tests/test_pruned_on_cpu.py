@@ -64,3 +64,29 @@ def test_a_group_that_no_plan_reaches_yet(program, tmp_path, S):
         p.M[0], p.M[1] = first, then
         for unit, records in SHAPES[:4]:
             check(program, tmp_path, p, unit, records)
+
+
+def broken(S, seed):
+    """Inputs that a solve refuses once it has run (device arrays are checked by its own kernels)."""
+    st = gi.Stream(40 + seed)
+    p = gi.random_instance(7300 + S + seed, 4, S, 600, M_rng=(0, 3), R_rng=(0.0, 4.0))
+    p.M[0] = 70
+    if seed == 0:
+        p.R[2] = np.nan                                   # more columns start to fit in a group than a wave keeps
+    else:
+        what = np.array([np.nan, -np.inf, np.inf, -1e30, -0.0, 1e38], np.float32)
+        for a, n in ((p.c.reshape(-1), 2 * seed), (p.R.reshape(-1), p.R.size // 2 ** seed)):
+            a[st.integers(n, 0, a.size - 1)] = what[st.integers(n, 0, 5)]
+        bad = np.array([-1, -2 ** 31, 2 ** 31 - 1, 601, 64], np.int64)
+        p.M.reshape(-1)[st.integers(6, 0, p.M.size - 1)] = bad[st.integers(6, 0, 4)]
+        p.R[2, st.integers(S // 2, 0, S - 1)] = np.nan
+    return p
+
+
+@pytest.mark.parametrize("S", [12, 40, 70, 130])
+def test_refused_inputs_are_read_and_written_in_range(program, tmp_path, S):
+    """NaN, negative and infinite costs and memories out of every range: whatever the values are, no
+    kernel leaves its buffers (the results are not looked at, the library hands none out)."""
+    for seed in range(5):
+        for unit, records in SHAPES:
+            run(program, tmp_path, broken(S, seed), unit, records)
