@@ -730,7 +730,11 @@ __global__ __launch_bounds__(256) void k_final_pruned(Tables t, int first, int u
         if (cand[c] == 0) continue;
         const bool in = (cand[c] >> lane) & 1;
         const float v = wave_min(in ? ub[c] : INFINITY);
-        if (v <= b) { b = v; a = 64 * c + __builtin_ctzll(__builtin_amdgcn_ballot_w64(in && ub[c] == v)); }
+        if (v <= b) {                                    // (b: as the lowest index has it, -0.0 and 0.0 are equal)
+          const int k = __builtin_ctzll(__builtin_amdgcn_ballot_w64(in && ub[c] == v));
+          b = lane_f(ub[c], k);
+          a = 64 * c + k;
+        }
       }
     } else {
       constexpr int NB = 8;

@@ -343,6 +343,16 @@ __device__ __forceinline__ int store_records(uint8_t* __restrict__ An, int EP, i
   return kNoGroupRecord;
 }
 
+// The two words of a group from its first and last value; true if they stand for its cells.  A zero does
+// not: costs of -0.0 are accepted, minima of equal sums keep the sign of the lowest index, and that may
+// change inside a group that begins and ends with the same zero.  Its words differ in sign, so that every
+// reader takes the cells.
+__device__ __forceinline__ bool words_of(float first, float last, float2& w) {
+  w = make_float2(first, last);
+  if (last == 0.0f) w = make_float2(first == 0.0f ? 0.0f : first, -0.0f);
+  return __float_as_int(w.x) == __float_as_int(w.y);
+}
+
 // Output s of a group in which no predecessor fits: +inf throughout, record 0.
 template <bool ARG>
 __device__ __forceinline__ void no_predecessor(const Tables& t, int inst, int row, int l, int wb, int s) {
@@ -394,11 +404,11 @@ __device__ __forceinline__ void rows(const Tables& t, int inst, int row, int l, 
     rk = in ? r[k] : rk;
     kk = in ? k : kk;
   }
-  const float fo = (estar == 0 ? tf : INFINITY) + cs, lo = tl + cs;
-  const bool same = __float_as_int(fo) == __float_as_int(lo);        // the cells are all equal: the words stand for them
+  float2 words;
+  const bool same = words_of((estar == 0 ? tf : INFINITY) + cs, tl + cs, words);   // the cells are all equal
   const bool none = tl == INFINITY;                                  // no predecessor fits: +inf throughout, record 0
   const bool one = estar == 0 && tf < INFINITY && __builtin_popcount(live) == 1;
-  if (valid) sum_table(t, inst, row, l)[(size_t)s * G + (wb >> 6)] = make_float2(fo, lo);
+  if (valid) sum_table(t, inst, row, l)[(size_t)s * G + (wb >> 6)] = words;
   int rec = 0;
   if (ARG) {
     const int own = __builtin_amdgcn_ds_bpermute(kk << 2, listv);
@@ -522,10 +532,11 @@ __device__ __forceinline__ void runs_of_rows(const Tables& t, int inst, int row,
     ++i;
   } while (todo);
   wave_sync();
-  const bool same = __float_as_int(fo) == __float_as_int(lo);        // the words stand for the cells
+  float2 words;
+  const bool same = words_of(fo, lo, words);
   const int first_arg = ARG ? __builtin_amdgcn_ds_bpermute(a0 << 2, listv) : 0;   // all lanes: inactive ones give nothing
   if (valid) {
-    sum_table(t, inst, row, l)[(size_t)s * G + (wb >> 6)] = make_float2(fo, lo);
+    sum_table(t, inst, row, l)[(size_t)s * G + (wb >> 6)] = words;
     if (ARG) {
       group_records(t, row)[(size_t)s * G + (wb >> 6)] = (uint8_t)(!same_arg ? kNoGroupRecord : a0 == KEEP ? 0 : first_arg);
     }
@@ -830,10 +841,10 @@ __device__ __forceinline__ void big_group(const Tables& t, int inst, int row, in
         tl = __builtin_fminf(tl, col[(v[i] >> 8) * 64 + n_in - 1] + r[i]);
       }
     }
-    const float fo = (estar == 0 ? tf : INFINITY) + cs, lo = tl + cs;
-    const bool same = __float_as_int(fo) == __float_as_int(lo);
+    float2 words;
+    const bool same = words_of((estar == 0 ? tf : INFINITY) + cs, tl + cs, words);
     const unsigned long long flat = __builtin_amdgcn_ballot_w64(same);
-    if (valid) sum_table(t, inst, row, l)[(size_t)s * G + (wb >> 6)] = make_float2(fo, lo);
+    if (valid) sum_table(t, inst, row, l)[(size_t)s * G + (wb >> 6)] = words;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int k = 64 * c + lane;

@@ -660,3 +660,23 @@ def test_a_slab_of_nan_is_refused_and_nothing_else_happens(g, S):
         for b in range(3):
             check_instance(g, ctx, p, b, full_C=False, q_es=[0, 70, 71, 127, 300, p.E])
         g.gbmw_destroy(ctx)
+
+
+@pytest.mark.parametrize("mode", ["records", "lazy-argmin"])
+@pytest.mark.parametrize("S", [65, 129, 255])
+def test_the_sign_of_a_zero_is_the_lowest_index_s(g, S, mode):
+    """Costs and transformations of -0.0 among zeros and positive ones: 0.0 and -0.0 are equal candidates, the
+    sum of the lowest index is kept with its sign; every cell, record, plan and the final reduce."""
+    E, parts = 700, []
+    for i, L in enumerate([4, 3, 2, 1]):
+        rs = np.random.RandomState(6000 + S + i)
+        p = gi.random_instance(6000 + S + i, L, S, E, M_rng=(0, 70), R_rng=(0.0, 1.0))
+        p.c[:] = np.where(rs.rand(L, S) < 0.5, np.float32(-0.0), np.where(rs.rand(L, S) < 0.6, np.float32(0.0), p.c))
+        p.R[:] = np.where(rs.rand(L, S, S) < 0.7, np.float32(-0.0), p.R)
+        parts.append(p)
+    p = gi.stack(parts, f"zeros-S{S}")
+    ctx = solve_gpu(p, flags=g.GBMW_FLAG_LAZY_ARGMIN if mode != "records" else g.GBMW_FLAG_KEEP_ALL_C, device_inputs=True)
+    for b in range(p.B):
+        _log(f"signed zeros S={S} {mode} instance {b}")
+        check_instance(g, ctx, p, b, full_C=True, q_es=list(range(0, E + 1, 13)))
+    g.gbmw_destroy(ctx)

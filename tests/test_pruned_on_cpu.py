@@ -90,3 +90,20 @@ def test_refused_inputs_are_read_and_written_in_range(program, tmp_path, S):
     for seed in range(5):
         for unit, records in SHAPES:
             run(program, tmp_path, broken(S, seed), unit, records)
+
+
+def signed_zeros(S, L, E, seed):
+    rs = np.random.RandomState(seed)
+    p = gi.random_instance(seed, L, S, E, M_rng=(0, 70), R_rng=(0.0, 1.0))
+    p.c[:] = np.where(rs.rand(*p.c.shape) < 0.5, np.float32(-0.0), np.where(rs.rand(*p.c.shape) < 0.6, np.float32(0.0), p.c))
+    p.R[:] = np.where(rs.rand(*p.R.shape) < 0.7, np.float32(-0.0), p.R)
+    return p
+
+
+@pytest.mark.parametrize("S", [9, 33, 65, 129])
+def test_the_sign_of_a_zero_is_the_lowest_index_s(program, tmp_path, S):
+    """Costs of -0.0 are accepted; 0.0 and -0.0 are equal candidates, and the sum of the lowest index is
+    kept with its sign, also where that changes inside a group that begins and ends alike."""
+    for seed, E in ((1, 5), (2, 127), (3, 500)):
+        for unit, records in ((0, 1), (1, 0), (4, 1)):
+            check(program, tmp_path, signed_zeros(S, 4, E, 100 * S + seed), unit, records)
