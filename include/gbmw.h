@@ -53,13 +53,18 @@ enum { GBMW_PTR_HOST = 0, GBMW_PTR_DEVICE = 1 };
 enum {
   GBMW_FLAG_KEEP_ALL_C = 1u,   /* keep every layer's fp32 table (default: last two) */
   GBMW_FLAG_TIME_KERNELS = 2u, /* record a HIP event pair around every min-plus launch
-                                  (implies GBMW_FLAG_ONE_STREAM)                       */
+                                  (implies GBMW_FLAG_ONE_STREAM and
+                                  GBMW_FLAG_LAYER_LAUNCHES; the kernels are those of a
+                                  solve of that problem with layer launches and without
+                                  this flag)                                             */
   GBMW_FLAG_ONE_STREAM = 4u,   /* enqueue every kernel on p->stream itself.  Default: the
                                   instances are split into groups whose per-layer
                                   launches run on library-owned helper streams of default
                                   priority that fork from and join back into p->stream
                                   with events, so the call is still ordered on p->stream
-                                  as a whole                                             */
+                                  as a whole.  The layer kernels are chosen by the number
+                                  of instances per launch, so this flag can change which
+                                  of them fill a small batch (identical results)         */
   GBMW_FLAG_RESOLVE_ALL = 8u,  /* gbmw_partition_search only: solve every stage of every
                                   live pair in every round                               */
   GBMW_FLAG_LAZY_ARGMIN = 16u  /* do not write the argmin records while the tables are
@@ -83,7 +88,9 @@ enum {
                                   exists to time the dense arithmetic                     */,
   GBMW_FLAG_COUNT_WORK = 64u   /* measurement: the min-plus launches also count the groups
                                   that read one column, for gbmw_last_solve_work
-                                  (implies GBMW_FLAG_ONE_STREAM).  The counts depend on the
+                                  (implies GBMW_FLAG_ONE_STREAM and
+                                  GBMW_FLAG_LAYER_LAUNCHES, with the kernels of a solve
+                                  without this flag).  The counts depend on the
                                   inputs alone; the counting costs registers, so time the
                                   kernels in a solve without this flag                    */,
   GBMW_FLAG_LAYER_LAUNCHES = 128u /* one launch per layer even for a small problem.

@@ -316,8 +316,11 @@ gbmw_status gbmw_detail::solve_batched(const gbmw_problem* p, uint32_t flags, gb
   TRY(c->d_status.reserve(sizeof(int)));
   const int RS = (SP + 2 + 3) / 4 * 4;
   TRY(c->d_C.reserve(sizeof(float) * slab * (keep ? (size_t)sumL : (size_t)2 * B)));
+  // A solve whose launches are timed or counted takes the kernels that it would take without that: they are
+  // chosen by the instances per launch, and those flags put all instances into one launch
+  const int Gd = (flags & GBMW_FLAG_ONE_STREAM) ? 1 : std::min(kGroups, B);
   const bool runs = (flags & GBMW_FLAG_DENSE_ARITHMETIC) == 0 && !single &&
-                    gbmw::pruned_step_takes(S, E, (B + G - 1) / G, 400000000ll / G);
+                    gbmw::pruned_step_takes(S, E, (B + Gd - 1) / Gd, 400000000ll / Gd);
   // the pruned step reads R as it comes, the dense kernels its transposed, padded form
   TRY(c->d_Rt.reserve(sizeof(float) * (size_t)sumL * S * (runs ? S : RS)));
   if (runs) TRY(c->d_row.reserve(sizeof(float4) * (size_t)sumL * S));

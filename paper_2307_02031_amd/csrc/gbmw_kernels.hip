@@ -513,13 +513,20 @@ struct Blocking {                       // budgets per lane for a given strategy
   static constexpr int MINW_RUNS = 5, MINW_RUNS_FIRST = 4;
 };
 
+// Groups of 64 budgets per launch from which a wave takes a group of its own instead of a fourth of one:
+// where workgroups of one group would come in more than two rounds of the five (beyond 64 strategies four or
+// three) that a compute unit holds.  A solve, four waves per group -> one: S=20, 2624 groups 244 -> 198 us and
+// 3078 groups 234 -> 177; S=255, 2052 groups 842 -> 640; below the line S=36, 2064 groups 215 -> 227 and S=66,
+// 1026 groups 177 -> 199.  (S=64 gains from 2800 on: 365 -> 383 at 2624, 324 -> 278 at 3078.)
+static long long wave_groups(int S) { return S <= 64 ? 2560 : 2048; }
+
 // The shape of a pruned launch: groups of 64 budgets per wave and workgroups per instance.
 struct PrunedShape { int unit, places; size_t lds; };
 static PrunedShape pruned_shape(const Tables& t, int n_active) {
   const int groups = (t.E + 64) / 64;
   PrunedShape p;
   const long long all = (long long)groups * n_active;
-  p.unit = (t.counts || all >= 16384) ? kUnit : all >= 4096 ? 1 : 0;
+  p.unit = (t.counts || all >= 16384) ? kUnit : all >= wave_groups(t.S) ? 1 : 0;
   p.places = p.unit == 0 ? groups : (groups + kWaves * p.unit - 1) / (kWaves * p.unit);
   p.lds = (size_t)pruned_lds_floats(t.S, kept(t.SP)) * sizeof(float);
   return p;
@@ -647,17 +654,20 @@ void launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t
 bool layer0_in_registers(const Tables& t) { return t.runs != 0 || t.S <= 64; }
 
 // When the pruned step is taken (else the dense kernels; the results are the same).  S == 256: a
-// strategy index of 255 would read as kNoGroupRecord.  Beyond 64 strategies always (the dense kernels
-// take 13 times as long at B=16, S=128, E=32768 and 3 times at B=4, S=186, E=16384).  Up to 64 it
-// takes 10 to 17 us per layer however small the launch is (a chain of memory round trips per group),
-// a split dense launch about 10 us plus its updates at 1.75e13 per second: they meet at about 4e8
-// updates per layer (B=37, S=21, E=4999, 8e7 updates: 276 us per solve pruned, 228 dense; B=64, S=44,
-// E=32768, 4e9: 0.85 ms and 3.2 ms).  Launches that the dense kernels would not split are larger in
-// groups and take it too.
+// strategy index of 255 would read as kNoGroupRecord.  Beyond 64 strategies the dense kernels take 1.1 to 30
+// times as long, but for up to 80 strategies over at most three groups of 64 budgets (S=65, E=64: 262 us per
+// solve dense, 321 pruned; S=80, E=128: 347 and 366; S=96, E=64: 464 and 315; S=65, E=200: 268 and 250).
+// Up to 64 the pruned step takes 10 to 17 us per layer however small the launch is (a chain of memory round
+// trips per group), a split dense launch about 10 us plus its updates at 1.75e13 per second.  Where they meet
+// depends on the costs: at 1.3e8 updates per layer with transformations up to a tenth of the layer costs
+// (S=24, E=16384, B=12: 168 us per solve dense, 163 pruned), at 6e8 to 1.3e9 with transformations above the
+// layer costs, which leave little out (S=64, E=5200, B=64: 852 and 829); 4e8 lies between.  From 2560 groups
+// per launch on, dense launches are no longer split and the pruned ones hold a group per wave: level at S=4
+// (150 and 145 us at 4160 groups), 1.3 times as fast at S=16.
 bool pruned_step_takes(int S, int E, int n, long long most_dense_updates) {
   if (S >= 256) return false;
-  if (S > 64) return true;
-  return (long long)((E + 256) / 256) * n >= 640 || (long long)n * (E + 1) * S * S >= most_dense_updates;
+  if (S > 64) return S > 80 || E >= 192;
+  return (long long)((E + 64) / 64) * n >= wave_groups(S) || (long long)n * (E + 1) * S * S >= most_dense_updates;
 }
 
 const char* minplus_variant(int S) {

@@ -391,12 +391,13 @@ using gbmw_detail::fail;
 namespace {
 
 // Most rounds of a search touch a few stages only, so its launches are smaller than its number of
-// stages says: the pruned layer step pays from more updates per layer on than in one solve (32 pairs
-// of 48 layers, S=22, E=16384, 9.5e8 updates if all 120 stages are solved: 9.6 ms pruned, 8.5 ms dense;
-// S=44, E=32768, 7.6e9: 10 ms and 16.6 ms).
+// stages says: the pruned layer step pays from more updates per layer on than in one solve.  Up to 64
+// strategies, dense and pruned in ms, by the updates of a layer of all stages: cost-model tables (S=22)
+// 9.5e8 7.0 and 8.0, 1.07e9 7.05 and 7.24, 1.22e9 7.47 and 7.35, 1.43e9 8.92 and 8.14, 1.9e9 10.6 and 9.3;
+// structured tables S=22 4.8e8 3.96 and 4.18, 9.5e8 4.82 and 4.54, S=44 9.5e8 4.62 and 5.01, 1.43e9 5.14 and
+// 5.07, 7.6e9 14.2 and 7.7.
 bool search_takes_pruned(int S, int E, int stages) {
-  return S > 64 ? gbmw::pruned_step_takes(S, E, stages, 0)
-                : gbmw::pruned_step_takes(S, E, stages, 0) && (long long)stages * (E + 1) * S * S >= 1500000000ll;
+  return gbmw::pruned_step_takes(S, E, stages, 0) && (S > 64 || (long long)stages * (E + 1) * S * S >= 1200000000ll);
 }
 
 struct Carver {

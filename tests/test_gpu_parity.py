@@ -680,3 +680,21 @@ def test_the_sign_of_a_zero_is_the_lowest_index_s(g, S, mode):
         _log(f"signed zeros S={S} {mode} instance {b}")
         check_instance(g, ctx, p, b, full_C=True, q_es=list(range(0, E + 1, 13)))
     g.gbmw_destroy(ctx)
+
+
+def test_measuring_flags_show_the_kernels_of_the_plain_call(g):
+    """A batch whose two instance groups take the dense kernels while all instances in one launch would take
+    the pruned step (ten instances of 1 to 5 layers, 3160 groups of 64 budgets together): counted, it
+    reports dense rows only; asked for one stream, it reports the step that a call on one stream takes."""
+    S, E = 9, 316 * 64 - 5
+    parts = [gi.random_instance(9500 + i, 1 + i % 5, S, E, M_rng=(1, 900)) for i in range(10)]
+    p = gi.stack(parts, "flags")
+    rows = int(sum(int(L) - 1 for L in p.L)) * 316 * S
+    ctx = solve_gpu(p, flags=g.GBMW_FLAG_COUNT_WORK, device_inputs=True)
+    assert g.gbmw_last_solve_work(ctx) == (0, 0, 0, rows)
+    check_instance(g, ctx, p, 4, full_C=False, q_es=[0, E // 2, E])
+    ctx = solve_gpu(p, flags=g.GBMW_FLAG_COUNT_WORK | g.GBMW_FLAG_ONE_STREAM, device_inputs=True, ctx=ctx)
+    wide, runs, _, dense = g.gbmw_last_solve_work(ctx)
+    assert wide + runs > 0 and dense < rows
+    check_instance(g, ctx, p, 4, full_C=False, q_es=[0, E // 2, E])
+    g.gbmw_destroy(ctx)
