@@ -353,14 +353,6 @@ __device__ __forceinline__ bool words_of(float first, float last, float2& w) {
   return __float_as_int(w.x) == __float_as_int(w.y);
 }
 
-// Output s of a group in which no predecessor fits: +inf throughout, record 0.
-template <bool ARG>
-__device__ __forceinline__ void no_predecessor(const Tables& t, int inst, int row, int l, int wb, int s) {
-  const size_t at = (size_t)s * (t.EP >> 6) + (wb >> 6);
-  sum_table(t, inst, row, l)[at] = make_float2(INFINITY, INFINITY);
-  if (ARG) group_records(t, row)[at] = 0;
-}
-
 // Cells, summaries and records of one group for the outputs s = sfirst + lane (valid lanes), given
 // the columns of its K <= KEEP candidates in LDS: lane k holds candidate k's strategy (listv, in
 // index order) and the place of its column (slotv).  estar: first budget of the group at which a
@@ -690,9 +682,12 @@ __device__ __forceinline__ bool dense_group(const Tables& t, int inst, int row, 
             bool live = false;
 #pragma unroll
             for (int oc = 0; oc < NCH; ++oc) {
-              const float x = lane_f(pass == 0 ? ub[c] : lb[c], k[i]) + r[i][oc];
-              if (pass == 0) tub[oc] = __builtin_fminf(tub[oc], x);
-              else live = live || (64 * oc + lane < S && x <= tub[oc]);
+              if (pass == 0) {
+                tub[oc] = __builtin_fminf(tub[oc], lane_f(ub[c], k[i]) + r[i][oc]);
+              } else {
+                const float x = lane_f(lb[c], k[i]) + r[i][oc];
+                live = live || (64 * oc + lane < S && x <= tub[oc]);
+              }
             }
             if (pass == 1 && __builtin_amdgcn_ballot_w64(live) != 0) keep |= 1ull << k[i];
           }
@@ -703,13 +698,10 @@ __device__ __forceinline__ bool dense_group(const Tables& t, int inst, int row, 
 #pragma unroll
     for (int c = 0; c < NCH; ++c) K += __builtin_popcountll(cand[c]);
     if (K > KEEP) return false;
-    if (K == 0) {
-      // only with entries of R that no comparison holds for (NaN: the solve is refused once it has run)
-#pragma unroll
-      for (int oc = 0; oc < NCH; ++oc)
-        if (part == 0 && 64 * oc + lane < S) no_predecessor<ARG>(t, inst, row, l, wb, 64 * oc + lane);
-      return true;
-    }
+    // emptied only by entries of R that no comparison holds for (NaN: the solve is refused once it has
+    // run): any one column will do
+    if (K == 0) cand[0] = 1;
+    K = K > 0 ? K : 1;
   }
 
   // sized to the candidates: the unrolled loops run for all of their slots
@@ -811,14 +803,14 @@ __device__ __forceinline__ void big_group(const Tables& t, int inst, int row, in
     if (in[c]) list[K2 + __builtin_popcountll(b & ((1ull << lane) - 1))] = (uint16_t)sk[c];
     K2 += __builtin_popcountll(b);
   }
+  // A column's words may speak for budgets beyond this group.  If no column is finite inside it after all, the
+  // list is as it was and its first one (+inf throughout) stands for them.
+  K2 = K2 > 0 ? K2 : 1;
   __syncthreads();
   const int per = (S + kWaves - 1) / kWaves;             // at most 64
   const int sfirst = wave * per;
   const bool valid = lane < per && sfirst + lane < S;
-  if (K2 == 0) {
-    // a column's words may speak for budgets beyond this group: no column is finite inside it after all
-    if (valid) no_predecessor<ARG>(t, inst, row, l, wb, sfirst + lane);
-  } else if (K2 <= KEEP) {
+  if (K2 <= KEEP) {
     const int v = (int)list[lane < K2 ? lane : K2 - 1];
     rows<KEEP, STAGED, ARG>(t, inst, row, l, wb, n_in, lane, K2, v & 255, v >> 8, estar, col, rt, sfirst, valid);
   } else {
