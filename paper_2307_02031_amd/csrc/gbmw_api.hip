@@ -454,7 +454,7 @@ gbmw_status gbmw_detail::solve_batched(const gbmw_problem* p, uint32_t flags, gb
         t.counts = (unsigned long long*)c->d_counts.p + 4 * (size_t)c->counted_launches++;
         c->counted_waves.push_back((unsigned long long)na * (unsigned long long)((E + 64) / 64));
       }
-      gbmw::launch_minplus(t, l, gfirst[g], na, sg);
+      HIP_TRY_B(gbmw::launch_minplus(t, l, gfirst[g], na, sg));
       if (timed) {
         HIP_TRY_B(hipEventRecord(c->ev_layer[2 * c->timed_launches + 1], sg));
         ++c->timed_launches;

@@ -180,8 +180,8 @@ bool layer0_in_registers(const Tables& t);
 bool pruned_step_takes(int S, int E, int n, long long most_dense_updates);
 // One layer l >= 1 for instances perm[first .. first + n_active):
 // min-plus product with argmin, fused with the shift by M(l,s), the + c(l,s)
-// and the +inf prefix.
-void launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t st);
+// and the +inf prefix.  An error if no kernel is there for these tables (nothing is launched).
+hipError_t launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t st);
 // best(e), best_s(e) for e = final_from .. E over the last layer of instances
 // perm[first .. first + count).
 void launch_final(const Tables& t, int first, int count, hipStream_t st);
@@ -228,7 +228,5 @@ struct PersistArgs {
 // holds at once (0: no such kernel).
 int layers_resident_workgroups(int S, int waves, bool records);
 hipError_t launch_layers(const Tables& t, const PersistArgs& a, int waves, bool cooperative, hipStream_t st);
-
-const char* minplus_variant(int S);
 
 }  // namespace gbmw

@@ -624,31 +624,33 @@ static void launch_minplus_big(const Tables& t, int l, int first, int n_active, 
                        l, tiles, first, make_deal(tiles, n_active));
 }
 
-void launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t st) {
-  if (n_active <= 0) return;
+hipError_t launch_minplus(const Tables& t, int l, int first, int n_active, hipStream_t st) {
+  if (n_active <= 0) return hipSuccess;
   if (t.runs != 0 && t.S > 64) {
     if (t.S <= 128) launch_pruned_wide<2>(t, l, first, n_active, st);
     else launch_pruned_wide<4>(t, l, first, n_active, st);
-    return;
+    return hipSuccess;
   }
   switch (t.SP) {
-#define GBMW_CASE(N) case N: launch_minplus_sp<N>(t, l, first, n_active, st); return;
+#define GBMW_CASE(N) case N: launch_minplus_sp<N>(t, l, first, n_active, st); return hipSuccess;
     GBMW_CASE(4) GBMW_CASE(8) GBMW_CASE(12) GBMW_CASE(16) GBMW_CASE(20) GBMW_CASE(24)
     GBMW_CASE(28) GBMW_CASE(32) GBMW_CASE(36) GBMW_CASE(40) GBMW_CASE(44) GBMW_CASE(48)
     GBMW_CASE(52) GBMW_CASE(56) GBMW_CASE(60) GBMW_CASE(64)
 #undef GBMW_CASE
   // (a launch of fewer waves than the chip has SIMDs is better off with the generic kernel below,
   // whose waves divide the output strategies: four times the waves)
-#define GBMW_CASE(N) case N: if ((long long)((t.E + 64) / 64) * n_active < 1024) break; launch_minplus_big<N>(t, l, first, n_active, st); return;
+#define GBMW_CASE(N) case N: if ((long long)((t.E + 64) / 64) * n_active < 1024) break; launch_minplus_big<N>(t, l, first, n_active, st); return hipSuccess;
     GBMW_CASE(68) GBMW_CASE(72) GBMW_CASE(76) GBMW_CASE(80) GBMW_CASE(84) GBMW_CASE(88)
     GBMW_CASE(92) GBMW_CASE(96) GBMW_CASE(100) GBMW_CASE(104) GBMW_CASE(108) GBMW_CASE(112)
     GBMW_CASE(116) GBMW_CASE(120) GBMW_CASE(124) GBMW_CASE(128)
 #undef GBMW_CASE
     default: break;
   }
+  if (t.runs != 0) return hipErrorInvalidDeviceFunction;   // the generic kernel reads t.Rt, which is not there
   const int tiles = (t.E + 64) / 64;
   hipLaunchKernelGGL(k_minplus_generic, dim3((unsigned)tiles * n_active), dim3(256),
                      (size_t)t.S * 64 * sizeof(float), st, t, l, tiles, first);
+  return hipSuccess;
 }
 
 bool layer0_in_registers(const Tables& t) { return t.runs != 0 || t.S <= 64; }
@@ -668,11 +670,6 @@ bool pruned_step_takes(int S, int E, int n, long long most_dense_updates) {
   if (S >= 256) return false;
   if (S > 64) return S > 80 || E >= 192;
   return (long long)((E + 64) / 64) * n >= wave_groups(S) || (long long)n * (E + 1) * S * S >= most_dense_updates;
-}
-
-const char* minplus_variant(int S) {
-  return S <= 128 ? "register-blocked, LDS-staged R tile, prefix-min value pass + on-demand argmin rescan"
-                  : "generic LDS-staged (S > 128)";
 }
 
 // ---------------------------------------------------------------------------

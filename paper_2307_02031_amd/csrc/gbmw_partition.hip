@@ -813,7 +813,7 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
         for (size_t x = 0; x < append.size();) {
           size_t y = x;
           while (y < append.size() && slotL[append[y]] == slotL[append[x]]) ++y;
-          gbmw::launch_minplus(t, slotL[append[x]] - 1, a_first + (int)x, (int)(y - x), sg);
+          HIP_TRY(gbmw::launch_minplus(t, slotL[append[x]] - 1, a_first + (int)x, (int)(y - x), sg));
           x = y;
         }
         gbmw::launch_final(t, a_first, (int)h_perm.size() - a_first, sg);
@@ -823,7 +823,7 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
       for (int l = 1; l < Lmax_g; ++l) {
         int na = 0;
         while (na < gn && slotL[h_perm[gfirst[g] + na]] > l) ++na;
-        gbmw::launch_minplus(t, l, gfirst[g], na, sg);
+        HIP_TRY(gbmw::launch_minplus(t, l, gfirst[g], na, sg));
       }
       gbmw::launch_final(t, gfirst[g], gn, sg);
       if (g > 0) {
