@@ -86,12 +86,13 @@ def cpu_baseline(p, budget_s=12.0):
 def kernel_roofline(g, torch, p, d, args, flags, step_sec):
     """The dominant kernel (k_minplus: Eq. 3's inner minimum fused with the shift-add), one launch per
     layer: average duration from HIP event pairs around every launch on the solve's stream (one stream),
-    and the work the launches really did from the library's path counters (a second, untimed solve
-    with GBMW_FLAG_COUNT_WORK: which groups read one column depends on the inputs alone).
+    and the work the launches did from the library's counters (a second, untimed solve with
+    GBMW_FLAG_COUNT_WORK: what the bounds leave depends on the inputs alone).
 
-    achieved = executed lane-ops per launch / average launch duration, with 2 lane-ops (one add, one
-    min) per candidate update that a lane or a run really computed; covered / executed updates is
-    the shortcut's gain and is reported separately.  HBM bytes are modelled from the same counters.
+    achieved = lane-ops per launch / average launch duration, with 2 lane-ops (one add, one min) per
+    candidate update: with dense arithmetic every one, by default those that the bounds leave (what a
+    launch computes at most: it forms some of them once for several budgets); covered / executed updates
+    is the bounds' gain and is reported separately.  HBM bytes are modelled with dense arithmetic only.
     """
     dense = bool(flags & g.GBMW_FLAG_DENSE_ARITHMETIC)
     keep = flags & (g.GBMW_FLAG_DENSE_ARITHMETIC | g.GBMW_FLAG_LAZY_ARGMIN)
@@ -114,9 +115,7 @@ def kernel_roofline(g, torch, p, d, args, flags, step_sec):
     g.gbmw_destroy(tctx)
     S = p.S
     tot = [sum(w[k] for w in work) for k in range(4)]
-    upd_runs = (tot[0] + tot[1] + tot[2]) * S * S                          # one column's S x S' updates each
-    upd_dense = tot[3] * 64 * S                                            # a row: 64 lanes x S' candidates
-    upd_exec = upd_runs + upd_dense
+    upd_exec = tot[3] * 64 * S if dense else tot[2]                        # a row: 64 lanes x S' candidates
     covered = p.executed_updates()
     # HBM bytes with dense arithmetic: per row (wave, s) 64 x 4 B of the previous table read (not in the
     # layer-1 launch), 64 x 4 B of the new table and 64 x 1 B of records written; the R tile of an instance's
@@ -128,8 +127,6 @@ def kernel_roofline(g, torch, p, d, args, flags, step_sec):
         read_b += int((p.L > i + 1).sum()) * 8 * S * RS * 4 + w[3] * (256 if i > 0 else 0)   # launch i is layer i + 1
         write_b += w[3] * (256 + 64 * rec)
     avg_launch_s = mp_ms / mp_n * 1e-3 if mp_n else float("nan")
-    # the default mode computes only the candidates that can still be minimal, which is not counted: the
-    # figures from the counters are exact with dense arithmetic and upper bounds (null here) without it
     ach = OPS_PER_UPDATE * upd_exec / n_launch / avg_launch_s / 1e12 if mp_n else 0.0
     hbm_model = (read_b + write_b) / n_launch if n_launch else 0.0
     traffic, traffic_source = None, None
@@ -147,23 +144,22 @@ def kernel_roofline(g, torch, p, d, args, flags, step_sec):
     return {
         "kernel": "k_minplus (fused min-plus + argmin + shift-add), one launch per layer",
         "mode": "dense arithmetic" if dense else "pruned layer step (default)",
-        "bound": "alu" if dense else "latency", "achieved": ach if dense else None, "peak": PEAK_PLAIN_FP32_TOPS, "unit": "TFLOP/s",
-        "frac": ach / PEAK_PLAIN_FP32_TOPS if dense else None,
+        "bound": "alu" if dense else "latency", "achieved": ach, "peak": PEAK_PLAIN_FP32_TOPS, "unit": "TFLOP/s",
+        "frac": ach / PEAK_PLAIN_FP32_TOPS,
         "peak_is": "plain (non-packed, non-FMA) fp32 VALU lane-ops: 256 CU x 64 lanes x 2.4 GHz = 39.3 T/s; "
                    "the published 157.3 TFLOP/s is this x2 packed x2 FMA",
-        "frac_of_published_fp32_vector_peak": ach / PEAK_PUBLISHED_FP32_TFLOPS if dense else None,
+        "frac_of_published_fp32_vector_peak": ach / PEAK_PUBLISHED_FP32_TFLOPS,
         "ops_per_update": OPS_PER_UPDATE,
         "valu_instr_floor_per_update": 1.5,
-        "frac_of_instr_floor": ach / OPS_PER_UPDATE * 1.5 / PEAK_PLAIN_FP32_TOPS if dense else None,
-        "note": "achieved = 2 lane-ops (add, min) x candidate updates really computed per launch / average "
-                "launch duration; a three-input min folds two candidates, so the instruction floor is 1.5 per "
+        "frac_of_instr_floor": ach / OPS_PER_UPDATE * 1.5 / PEAK_PLAIN_FP32_TOPS,
+        "note": "achieved = 2 lane-ops (add, min) x candidate updates (dense arithmetic: all; default: those that "
+                "the bounds leave) per launch / average launch duration; a three-input min folds two candidates, so the instruction floor is 1.5 per "
                 "update and frac_of_instr_floor is the share of the VALU issue rate that floor would need",
-        "executed_updates_per_launch": upd_exec / n_launch if n_launch and dense else None,
-        "executed_updates_per_launch_at_most": upd_exec / n_launch if n_launch else 0,
+        "executed_updates_per_launch": upd_exec / n_launch if n_launch else 0,
         "covered_updates_per_launch": covered / n_launch if n_launch else 0,
-        "shortcut_gain_at_least": covered / upd_exec if upd_exec else None,
-        "work_per_solve": {"run_workgroups": tot[0], "run_waves_by_summary": tot[1], "run_waves_by_value": tot[2],
-                           "dense_rows": tot[3]},
+        "shortcut_gain": covered / upd_exec if upd_exec else None,
+        "work_per_solve": {"one_column_units_of_256": tot[0], "other_one_column_groups": tot[1],
+                           "updates_left_by_the_bounds": tot[2], "rows_of_other_groups": tot[3]},
         "hbm": {"modelled_bytes_per_launch": hbm_model if dense else None,
                 "achieved_GBps": hbm_model / avg_launch_s / 1e9 if mp_n and dense else None,
                 "peak": 8000.0, "frac": hbm_model / avg_launch_s / 8e12 if mp_n and dense else None,

@@ -510,12 +510,12 @@ gbmw_status gbmw_last_solve_ms(gbmw_ctx* ctx, float* total_ms, float* minplus_ms
  * budgets read one and the same column of the previous table:
  *   work[0]  units of 256 budgets that are one run
  *   work[1]  other groups of 64 budgets that are a run
- *   work[2]  0
- *   work[3]  (group, output strategy) rows of the groups that are not a run.  With
- *            GBMW_FLAG_DENSE_ARITHMETIC (and where the dense kernels are taken by
- *            themselves) every row of the tables: 64 * S candidate updates each.  By
- *            default only the candidates that can still be minimal are computed, so
- *            64 * S is an upper bound there
+ *   work[2]  candidate updates that the default mode's bounds leave, what it computes at
+ *            most: per group the predecessors that can still be minimal in it, times S,
+ *            times its budgets unless all of those are constant over it.  0 with
+ *            GBMW_FLAG_DENSE_ARITHMETIC and where the dense kernels are taken by themselves
+ *   work[3]  (group, output strategy) rows of the groups that are not a run; with the
+ *            dense kernels every row of the tables, 64 * S candidate updates each
  * Waits for the solve.
  */
 gbmw_status gbmw_last_solve_work(gbmw_ctx* ctx, int32_t launch, uint64_t work[4]);

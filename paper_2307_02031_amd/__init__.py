@@ -379,8 +379,9 @@ def gbmw_last_solve_ms(ctx: Context):
 
 
 def gbmw_last_solve_work(ctx: Context, launch: int = -1):
-    """(wide workgroups, run waves by summary, run waves by value, dense rows) of the last counted
-    solve: of one min-plus launch, or summed over all (launch = -1)."""
+    """(units of 256 budgets that read one column, other groups of 64 that do, candidate updates that the
+    bounds leave, rows of the groups that read several columns) of the last counted solve: of one min-plus
+    launch, or summed over all (launch = -1)."""
     w = (ct.c_uint64 * 4)()
     _check(_lib.gbmw_last_solve_work(ctx.handle, launch, w))
     return tuple(int(x) for x in w)

@@ -774,7 +774,7 @@ gbmw_status gbmw_last_solve_work(gbmw_ctx* c, int32_t launch, uint64_t work[4]) 
   for (int i = 0; i < c->counted_launches; ++i) {
     if (launch >= 0 && i != launch) continue;
     work[0] += h[4 * i]; work[1] += h[4 * i + 1]; work[2] += h[4 * i + 2];
-    covered += h[4 * i + 1] + h[4 * i + 2] + h[4 * i + 3];
+    covered += h[4 * i + 1] + h[4 * i + 3];
     waves += c->counted_waves[i];
   }
   work[3] = (waves - covered) * (uint64_t)c->S;

@@ -56,12 +56,11 @@ struct Tables {
   float* best;         // [B][EP]
   uint8_t* best_s;     // [B][EP]
   int* status;         // device word; bit 0: bad c, bit 1: bad M, bit 2: bad R
-  unsigned long long* counts;  // null, or four counters of the launch, for measurements: [0] workgroups
-                       // whose four waves shared one column (S * S' updates computed per workgroup)
-                       // and [3] the waves inside the table that those workgroups covered;
-                       // [1] waves recognised as a run from the summaries and [2] from the loaded
-                       // table values (S * S' updates per wave).  Every other wave inside the table
-                       // computed its 64 * S cells one by one
+  unsigned long long* counts;  // null, or four counters of a launch of the pruned step, for measurements:
+                       // [0] units of 256 budgets that read one column and [3] the groups of 64 inside
+                       // the table that they cover; [1] other groups of 64 budgets that read one column;
+                       // [2] candidate updates that the bounds leave: candidates * S per group that is
+                       // constant in all of them, times its budgets elsewhere
 };
 
 #if defined(__HIPCC__)
@@ -171,7 +170,7 @@ void launch_prepare(const Tables& t, const float* R, const float* src_c, const i
 void launch_clear_counts(unsigned long long* counts, int n, hipStream_t st);
 // C(0, e, s) written to the table for instances perm[first .. first + count).  Needed
 // where something reads layer 0 from memory: instances with L_b <= 2 (final reduce,
-// export), every instance when all layers are kept or S > 64.
+// export), every instance when all layers are kept or the dense kernels fill S > 64.
 void launch_init_layer0(const Tables& t, int first, int count, hipStream_t st);
 // True when the layer-1 launch builds layer 0 in registers and does not read it.
 bool layer0_in_registers(const Tables& t);

@@ -900,7 +900,7 @@ __device__ __forceinline__ void big_group(const Tables& t, int inst, int row, in
 
 // Measurement only: which groups of the unit read one and the same column of the previous table
 // at all their budgets.  counts[0] / [3]: whole units of 256 budgets and the groups inside the
-// table that they cover; [1]: other such groups.
+// table that they cover; [1]: other such groups.  ([2]: see pruned_step.)
 template <bool FIRST>
 __device__ __forceinline__ void count_runs(const Tables& t, int inst, int row, int l, int base, int lane) {
   const int S = t.S, E = t.E;
@@ -1034,6 +1034,12 @@ __device__ __forceinline__ void pruned_step(const Tables& t, int l, int2 who, in
       unsigned long long cand[NCH];
       bool varies;
       bounds<NCH>(q, wb, el, ub, lb, cand, varies);
+      if (COUNT) {                                       // measurement only: the sums that the bounds leave
+        int left = 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) left += __builtin_popcountll(cand[c]);
+        if (lane == 0) atomicAdd(t.counts + 2, (unsigned long long)left * S * (varies ? el - wb + 1 : 1));
+      }
       if (varies) {
         mine = wb;
         if (share && lane == 0) x_group[atomicAdd(&x_n[0], 1)] = wb;

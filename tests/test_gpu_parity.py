@@ -698,3 +698,25 @@ def test_measuring_flags_show_the_kernels_of_the_plain_call(g):
     assert wide + runs > 0 and dense < rows
     check_instance(g, ctx, p, 4, full_C=False, q_es=[0, E // 2, E])
     g.gbmw_destroy(ctx)
+
+
+def test_counted_updates_left_by_the_bounds(g):
+    """work[2] of gbmw_last_solve_work: with one strategy its predecessor is left in every group that it reaches,
+    for all the group's budgets where its table begins inside it and once where it is constant; with nine,
+    the launches add up to the whole and leave less than every update of the groups that vary."""
+    E = 2600 * 64 + 9
+    for m in (0, 1, 63, 64, 1000, E):
+        p = gi.Problem(1, 1, E, np.array([2]), np.ones((2, 1), np.float32), np.array([[m], [3]]), np.zeros((2, 1, 1), np.float32))
+        ctx = solve_gpu(p, flags=g.GBMW_FLAG_COUNT_WORK, device_inputs=True)
+        first, groups = m // 64, E // 64 + 1
+        varies = 0 if m % 64 == 0 else min(64, E + 1 - 64 * first)
+        assert g.gbmw_last_solve_work(ctx)[2] == varies + groups - first - (1 if varies else 0), m
+        g.gbmw_destroy(ctx)
+    S = 9
+    p = gi.stack([gi.random_instance(9400 + i, L, S, E, M_rng=(1, 900)) for i, L in enumerate([4, 3])], "left")
+    ctx = solve_gpu(p, flags=g.GBMW_FLAG_COUNT_WORK, device_inputs=True)
+    whole = g.gbmw_last_solve_work(ctx)
+    each = [g.gbmw_last_solve_work(ctx, i) for i in range(3)]
+    assert tuple(sum(w[k] for w in each) for k in range(4)) == whole
+    assert 0 < whole[2] < (4 * whole[0] + whole[1]) * S * S + whole[3] * 64 * S
+    g.gbmw_destroy(ctx)
