@@ -71,11 +71,11 @@ SHAPES = [  # (S, E, list of L): ragged tails, tile boundaries, every kernel var
     (55, 1025, [2, 4]),
     (58, 800, [4, 2]),
     (64, 1500, [4, 6]),
-    (65, 500, [3, 2]),       # 65..128: register-blocked in larger workgroups (8 or 12 waves)
+    (65, 500, [3, 2]),
     (100, 300, [3]),
     (97, 1700, [3, 2]),
     (128, 2000, [2, 4]),
-    (129, 300, [3]),         # above 128: LDS-staged generic kernel
+    (129, 300, [3]),         # 65..255 are filled by the pruned step, 256 by the LDS-staged generic kernel
     (256, 130, [2, 3]),
 ]
 
@@ -111,15 +111,16 @@ def test_ragged_batches_all_shapes(g, S, E, Ls, device_inputs, lazy, extra):
     g.gbmw_destroy(ctx)
 
 
+@pytest.mark.parametrize("dense", [False, True], ids=["default", "dense"])
 @pytest.mark.parametrize("lazy", [False, True], ids=["records", "lazy-argmin"])
 @pytest.mark.parametrize("S", [3, 7, 11, 15, 19, 23, 26, 30, 34, 39, 43, 47, 51, 54, 59, 62])
-def test_wide_launches_every_instantiation(g, S, lazy):
-    """Launches of 640 workgroups and more take the kernel's other path (each wave owns
-    its own 64 budgets instead of sharing a tile with the other waves of its workgroup):
-    ten instances of E = 32805 for every register-blocked instantiation, with
-    integer-valued costs so that ties are everywhere."""
+def test_wide_launches_every_instantiation(g, S, lazy, dense):
+    """Ten instances of E = 32805 for every size of the kernels up to 64 strategies, with integer-valued
+    costs so that ties are everywhere.  Default: the pruned step, layer 1 with a group of 64 budgets per wave
+    (5 x 513 groups per stream), the later launches with four waves per group.  Dense: the register-blocked
+    kernel with 64 budgets of its own per wave (launches of 640 workgroups and more)."""
     E = 32805
-    _log(f"wide S={S}")
+    _log(f"wide S={S} dense={dense}")
     st = gi.Stream(6000 + S)
     parts = []
     for i, L in enumerate([3, 3, 3, 3, 3, 3, 3, 3, 3, 2]):
@@ -128,7 +129,8 @@ def test_wide_launches_every_instantiation(g, S, lazy):
         R = st.integers(L * S * S, 0, 2).astype(np.float32).reshape(L, S, S)
         parts.append(gi.Problem(1, S, E, np.array([L]), c, M, R))
     p = gi.stack(parts, f"wide-S{S}")
-    ctx = solve_gpu(p, flags=g.GBMW_FLAG_LAZY_ARGMIN if lazy else 0, device_inputs=True)
+    ctx = solve_gpu(p, flags=(g.GBMW_FLAG_LAZY_ARGMIN if lazy else 0) | (g.GBMW_FLAG_DENSE_ARITHMETIC if dense else 0),
+                    device_inputs=True)
     best, best_s = g.gbmw_get_best(ctx)
     for b in (0, 4, 9):
         check_instance(g, ctx, p, b, full_C=False, q_es=[0, 1, E // 2, E - 1, E], best=best, best_s=best_s)
@@ -140,14 +142,16 @@ def test_wide_launches_every_instantiation(g, S, lazy):
 
 
 @pytest.mark.parametrize("lazy", [False, True], ids=["records", "lazy-argmin"])
-@pytest.mark.parametrize("S", [65, 68, 83, 96, 97, 113, 128])
-def test_wide_launches_above_64_strategies(g, S, lazy):
-    """65 to 128 strategies in launches of at least 1024 waves take the register-blocked kernel in
-    workgroups of eight or twelve waves (smaller launches and larger S the generic one): seven
-    instances of 2 or 3 layers, a ragged last workgroup, integer costs (ties everywhere), every
-    table cell of three instances and the best rows of all against the oracle."""
+@pytest.mark.parametrize("S,dense", [(S, False) for S in (65, 68, 83, 96, 97, 113, 128)]
+                         + [(S, True) for S in (65, 68, 83, 96, 97, 113, 128, 129, 200, 255)])
+def test_wide_launches_above_64_strategies(g, S, lazy, dense):
+    """Seven instances of 2 or 3 layers beyond 64 strategies, a ragged last workgroup, integer costs (ties
+    everywhere), every table cell of three instances and the best rows of all against the oracle.  Default:
+    the pruned step with four waves per group.  Dense, all instances in one launch (at least 1024 waves of 64
+    budgets): the register-blocked kernel in workgroups of eight or twelve waves up to 128 strategies, the
+    generic one beyond."""
     E = 12000 + S
-    _log(f"wide S={S} lazy={lazy}")
+    _log(f"wide S={S} lazy={lazy} dense={dense}")
     st = gi.Stream(6500 + S)
     parts = []
     for i, L in enumerate([3, 3, 3, 3, 3, 3, 2]):
@@ -156,7 +160,8 @@ def test_wide_launches_above_64_strategies(g, S, lazy):
         R = st.integers(L * S * S, 0, 2).astype(np.float32).reshape(L, S, S)
         parts.append(gi.Problem(1, S, E, np.array([L]), c, M, R))
     p = gi.stack(parts, f"wide-S{S}")
-    ctx = solve_gpu(p, flags=g.GBMW_FLAG_LAZY_ARGMIN if lazy else g.GBMW_FLAG_KEEP_ALL_C, device_inputs=True)
+    ctx = solve_gpu(p, flags=(g.GBMW_FLAG_LAZY_ARGMIN if lazy else g.GBMW_FLAG_KEEP_ALL_C)
+                    | (g.GBMW_FLAG_DENSE_ARITHMETIC | g.GBMW_FLAG_ONE_STREAM if dense else 0), device_inputs=True)
     best, best_s = g.gbmw_get_best(ctx)
     for b in (0, 3, 6):
         check_instance(g, ctx, p, b, full_C=True, q_es=[0, 1, E // 2, E - 1, E], best=best, best_s=best_s)
@@ -565,18 +570,11 @@ def test_config5_all_modes_agree(g):
                 assert np.array_equal(x.view(np.uint8), y.view(np.uint8)), (mode, what)
 
 
-
-@pytest.mark.parametrize("mode", ["records", "lazy-argmin"])
-@pytest.mark.parametrize("S", [3, 8, 16, 17, 24, 40, 64, 65, 130, 255])
-def test_pruned_step_where_plans_start_to_fit(g, S, mode):
-    """The layer step that looks only at the candidates that can still be minimal, where its bounds
-    are weakest: columns that become finite inside a group of 64 budgets, at its edges and beyond E,
-    memories shared by many strategies (up to S candidates in one group: more than a wave keeps),
-    transformation costs far above the layer costs (nothing can be left out) and all equal (ties),
-    forbidden strategies, a last group of a few budgets.  Every cell, record and plan against the
-    oracle; launches of 720 x 64 budgets (large) down to one instance (small).  Bit-exact: the bounds
-    only leave out sums that are strictly larger in fp32."""
-    E = 11 * 256 - 250 if S > 64 else 90 * 256 - 13
+def plans_start_to_fit(S, E):
+    """Eight instances of 3 or 4 layers whose columns become finite inside a group of 64 budgets, at its edges and
+    beyond E, with memories shared by many strategies (up to S candidates in one group: more than a wave
+    keeps), transformation costs far above the layer costs (nothing can be left out) and all equal (ties),
+    forbidden strategies, a last group of a few budgets."""
     st = gi.Stream(6100 + S)
     parts = []
     for i in range(8):
@@ -599,7 +597,18 @@ def test_pruned_step_where_plans_start_to_fit(g, S, mode):
         if i == 5:
             M[0] = E + 1                             # nothing fits
         parts.append(gi.Problem(1, S, E, np.array([L]), c, M, R))
-    p = gi.stack(parts, f"pruned-S{S}")
+    return parts
+
+
+@pytest.mark.parametrize("mode", ["records", "lazy-argmin"])
+@pytest.mark.parametrize("S", [3, 8, 16, 17, 24, 40, 64, 65, 130, 255])
+def test_pruned_step_where_plans_start_to_fit(g, S, mode):
+    """The layer step that looks only at the candidates that can still be minimal, where its bounds
+    are weakest.  Every cell, record and plan against the oracle; up to 64 strategies in launches of 2880
+    groups of 64 budgets (one per wave) and of 720 (four waves share one), beyond in small ones.  Bit-exact:
+    the bounds only leave out sums that are strictly larger in fp32."""
+    E = 11 * 256 - 250 if S > 64 else 90 * 256 - 13
+    p = gi.stack(plans_start_to_fit(S, E), f"pruned-S{S}")
     lazy = mode == "lazy-argmin"
     ctx = solve_gpu(p, flags=(g.GBMW_FLAG_LAZY_ARGMIN if lazy else g.GBMW_FLAG_KEEP_ALL_C) | g.GBMW_FLAG_ONE_STREAM,
                     device_inputs=True)
@@ -607,6 +616,54 @@ def test_pruned_step_where_plans_start_to_fit(g, S, mode):
     for b in range(p.B):
         _log(f"pruned S={S} {mode} instance {b}")
         check_instance(g, ctx, p, b, full_C=True, q_es=[0, 63, 64, 700, E - 1, E], best=best, best_s=best_s)
+    g.gbmw_destroy(ctx)
+
+
+@pytest.mark.parametrize("mode", ["records", "lazy-argmin"])
+@pytest.mark.parametrize("copies", [5, 32], ids=["one-group-waves", "four-group-waves"])
+@pytest.mark.parametrize("S", [8, 16, 17, 40, 64, 65, 128, 130, 255])
+def test_pruned_step_in_its_large_launches(g, S, copies, mode):
+    """The same eight instances over 65 groups (the last of 42 budgets), copied until the first launches hold
+    a group per wave (40 x 65 groups: the waves of a workgroup share what is not constant beyond 64
+    strategies) and four (256 x 65: they share it always); the last launch has a quarter of the instances and
+    the next smaller shape.  Every cell, record and plan of the eight, the best rows of all copies."""
+    E = 64 * 64 + 41
+    p = gi.stack(plans_start_to_fit(S, E) * copies, f"large-S{S}")
+    _log(f"large launches S={S} copies={copies} {mode}")
+    ctx = solve_gpu(p, flags=(g.GBMW_FLAG_LAZY_ARGMIN if mode != "records" else g.GBMW_FLAG_KEEP_ALL_C)
+                    | g.GBMW_FLAG_ONE_STREAM, device_inputs=True)
+    best, best_s = g.gbmw_get_best(ctx)
+    for b in range(8):
+        check_instance(g, ctx, p, b, full_C=True, q_es=[0, 63, 64, 700, E - 1, E], best=best, best_s=best_s)
+        for copy in range(b + 8, p.B, 8):
+            assert np.array_equal(best[copy].view(np.uint32), best[b].view(np.uint32)) and np.array_equal(best_s[copy], best_s[b])
+    g.gbmw_destroy(ctx)
+
+
+@pytest.mark.parametrize("mode", ["records", "lazy-argmin"])
+@pytest.mark.parametrize("S,E,copies", [(7, 0, 520), (7, 5, 520), (7, 63, 520), (7, 64, 520), (7, 100, 520), (20, 127, 520),
+                                        (90, 0, 420), (90, 63, 420), (90, 64, 420), (130, 100, 420), (7, 100, 1700)])
+def test_pruned_step_over_one_and_two_groups(g, S, E, copies, mode):
+    """Tables of one or two groups of 64 budgets, the last of them short or a single budget, in launches that
+    are large only in instances: most waves of a workgroup lie beyond the table.  Five instances of 2 to 4
+    layers with integer costs, copied; every cell, record and plan of the five, the best rows of all."""
+    st = gi.Stream(8900 + E + S)
+    parts = []
+    for i in range(5):
+        L = 2 + i % 3
+        c = st.integers(L * S, 1, 5).astype(np.float32).reshape(L, S)
+        M = st.integers(L * S, 0, max(1, E // 3)).reshape(L, S)
+        R = st.integers(L * S * S, 0, 2).astype(np.float32).reshape(L, S, S)
+        parts.append(gi.Problem(1, S, E, np.array([L]), c, M, R))
+    p = gi.stack(parts * copies, f"few-groups-S{S}E{E}")
+    _log(f"few groups S={S} E={E} copies={copies} {mode}")
+    ctx = solve_gpu(p, flags=(g.GBMW_FLAG_LAZY_ARGMIN if mode != "records" else g.GBMW_FLAG_KEEP_ALL_C)
+                    | g.GBMW_FLAG_ONE_STREAM, device_inputs=True)
+    best, best_s = g.gbmw_get_best(ctx)
+    for b in range(5):
+        check_instance(g, ctx, p, b, full_C=True, q_es=list(range(E + 1)), best=best, best_s=best_s, nthreads=2)
+        for copy in range(b + 5, p.B, 5):
+            assert np.array_equal(best[copy].view(np.uint32), best[b].view(np.uint32)) and np.array_equal(best_s[copy], best_s[b])
     g.gbmw_destroy(ctx)
 
 

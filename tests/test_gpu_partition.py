@@ -122,8 +122,8 @@ def test_large_launch_extends_tables_that_small_launches_produced(g):
     """Eight pairs whose long first stage (10 layers) takes one more layer at its end after the
     first search.  In the first round the deep layers of those stages run in small launches
     (four stages per stream group: the shape in which the waves of a workgroup share a tile);
-    the extension runs as ONE launch over all eight (the shape with the shortcut for runs of
-    equal columns), which decides from the summaries the small launches left.  Traces against
+    the extension runs as ONE launch over all eight (64 budgets per wave), on the dense kernels at
+    this size (the pruned step's kept tables: the next test).  Traces against
     the oracle, with and without records, and the count of executed layer steps."""
     E = 32768
     models = []
@@ -140,6 +140,39 @@ def test_large_launch_extends_tables_that_small_launches_produced(g):
         assert all(list(res["p"][k, 1, :2]) == [11, 2] for k in range(8))
         # first round 8 x (9 + 2) steps; second 8 x (1 + 1); the last pair goes on to [12, 1]: 1 + 0
         assert res["cell_updates"] == (88 + 16 + 1) * (E + 1) * 25, res["cell_updates"]
+    g.gbmw_destroy(ctx)
+
+
+@pytest.mark.parametrize("split", [False, True], ids=["plain", "overall-memory"])
+@pytest.mark.parametrize("S,E,copies,tight", [(32, 32768, 3, 6), (70, 2500, 1, 9)])
+def test_kept_tables_of_the_pruned_step(g, S, E, copies, tight, split):
+    """Searches that take the pruned layer step (1.2e9 updates per layer up to 64 strategies, all beyond): stages
+    that gain a layer at their end, extended from the words of kept tables, stages that lose their last one
+    (only the final reduce again) and stages solved again, with and without records and, with O_b / O_ms
+    tables, from a first budget of the final reduce that is no multiple of 64.  Six models, copied; traces
+    of the six against the oracle, the copies alike."""
+    models = []
+    for k in range(6):
+        mod = gi.random_pipeline_model(1900 + 7 * S + k, 6 if S < 64 else 9, S, 2, E=E, m=4,
+                                       M_rng=(E * 3 // (20 * tight), E // tight),
+                                       R_rng=(0.0, 0.5), with_pt=False)
+        heavy = slice(-2, None) if k % 2 else slice(0, 2)   # the second or the first stage becomes the slowest
+        mod.c[heavy] *= 6.0; mod.c_ns[heavy] *= 6.0
+        mod.p0 = np.array([mod.Lm // 2, mod.Lm - mod.Lm // 2], np.int32)
+        models.append(gi.with_memory_split(mod, 1950 + k, ob_max=E // 9) if split else mod)
+    ctx, keys = None, ("n_iter", "O_t", "p", "cost", "C", "Cns", "O", "alpha_t", "alpha_m", "strat")
+    for flags in (0, g.GBMW_FLAG_LAZY_ARGMIN, g.GBMW_FLAG_DENSE_ARITHMETIC):
+        res, ctx = _search(g, models * copies, max_iter=8, flags=flags, ctx=ctx)
+        for key in keys:
+            for copy in range(1, copies):
+                assert np.array_equal(res[key][:6].view(np.uint8), res[key][6 * copy:6 * copy + 6].view(np.uint8)), (flags, key)
+        if flags == 0:
+            first = {key: res[key][:6] for key in keys}
+            check_partition_search(first, models, 8)
+            assert (res["n_iter"][:6] > 1).sum() >= 4, "the models must exercise the adjustment"
+            ref = res
+        for key in keys:
+            assert np.array_equal(ref[key].view(np.uint8), res[key].view(np.uint8)), (flags, key)
     g.gbmw_destroy(ctx)
 
 
@@ -229,9 +262,8 @@ def test_outer_loops_throughput(g):
 
 def test_benchmark_workload_all_modes_agree(g):
     """The workload bench.py times (16 pairs, 48 layers, S = 44, E = 32768): kept tables,
-    every stage re-solved, no argmin records, and dense arithmetic (no shortcut for waves whose
-    budgets share one input column) give the same traces bit for bit, with and without
-    O_b / O_ms tables; the
+    every stage re-solved, no argmin records, and dense arithmetic (every candidate in every
+    cell) give the same traces bit for bit, with and without O_b / O_ms tables; the
     first pair is also checked against the oracle."""
     import importlib.util
     import os
