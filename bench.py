@@ -281,8 +281,7 @@ def main():
                     help="instead of the benchmark, run a plain 1 GiB device-to-device copy five times "
                          "(a kernel of known traffic against which HBM byte counters are scaled)")
     ap.add_argument("--dense-arithmetic", action="store_true",
-                    help="GBMW_FLAG_DENSE_ARITHMETIC for every solve: no shortcut for waves whose budgets "
-                         "share one input column")
+                    help="GBMW_FLAG_DENSE_ARITHMETIC for every solve: every candidate in every cell")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-others", action="store_true", help="skip the short runs of the other configs")
     ap.add_argument("--no-partition", action="store_true", help="skip the partition-search leg (Algorithm 2)")

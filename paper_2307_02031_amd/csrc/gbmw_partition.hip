@@ -740,7 +740,7 @@ extern "C" gbmw_status gbmw_partition_search(const gbmw_partition_problem* q, ui
         }
         cell_updates += (long long)(L - 1) * (E + 1) * S * S;
         // what a complete solve leaves in the rolling pair: L-1 and L-2, layer 0 only if it
-        // was written to memory (stages of one or two layers, or S > 64)
+        // was written to memory (stages of one or two layers, or the dense kernels beyond 64 strategies)
         c_hi[b] = L - 1;
         c_lo[b] = (L >= 2 && (L - 2 >= 1 || L <= 2 || !l0_in_regs)) ? L - 2 : -1;
         if (lazy) c_lo[b] = 0;                       // every layer's table is kept: [c_lo, c_hi]

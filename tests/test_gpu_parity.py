@@ -272,12 +272,12 @@ def test_non_default_stream(g):
 def test_device_inputs_may_be_overwritten_after_the_solve(g):
     """The caller's device arrays are read by the solve's own enqueued work only: once a
     waiting call has returned they are overwritten with garbage here, and the walkers, the
-    export (which rebuilds cells from M under the run shortcut), Algorithm 3's loop and the
-    pipeline cost still give the oracle's results, with and without records."""
+    export (which rebuilds the cells of constant groups from M and their words), Algorithm 3's loop
+    and the pipeline cost still give the oracle's results, with and without records."""
     import torch
     for flags in (0, g.GBMW_FLAG_LAZY_ARGMIN):
-        # 700 row tiles x 2 instances: unsplit launches with the run shortcut; integer costs and
-        # coarse memories, so that most cells are left to their summary words
+        # 2800 groups of 64 budgets per launch: the pruned step; integer costs and coarse memories,
+        # so that most cells are left to their summary words
         E, S = 700 * 256 - 13, 6
         st = gi.Stream(9100)
         parts = []
@@ -307,11 +307,10 @@ def test_device_inputs_may_be_overwritten_after_the_solve(g):
 
 
 def test_work_counters_match_the_tables(g):
-    """GBMW_FLAG_COUNT_WORK: the number of (wave, strategy) rows that the launches report as
-    computed cell by cell is what the oracle's tables imply: a wave of 64 budgets escapes the
-    dense arithmetic exactly when the 64 columns of the previous layer's table that it reads are
-    the same bits (the kernel finds such waves from its summaries or, failing that, from the
-    loaded values), and the counted solve returns the same tables as the plain one."""
+    """GBMW_FLAG_COUNT_WORK: the number of (group, strategy) rows that the launches report as no run
+    is what the oracle's tables imply: a group of 64 budgets is a run exactly when the 64 columns
+    of the previous layer's table that it reads are the same bits, and the counted solve returns
+    the same tables as the plain one."""
     S, E = 9, 700 * 256 - 141
     st = gi.Stream(9300)
     parts = []
@@ -389,12 +388,12 @@ MODES = {"records": 0, "lazy-argmin": 16, "records-dense": 32, "lazy-argmin-dens
 @pytest.mark.parametrize("mode", list(MODES), ids=list(MODES))
 @pytest.mark.parametrize("S", [5, 44, 61])
 def test_runs_of_equal_columns_edge_cases(g, S, mode):
-    """By default a wave whose 64 budgets read the same column of the previous table computes
-    it once.  Layer-0 memories are placed so that the columns change exactly at, just before
-    and just after the wave boundaries (budgets 63, 64, 65, 127, 128, ...), at budget 0, at E
-    and beyond E, in unsplit launches (>= 640 workgroups) whose last wave is cut by E; later
-    layers shift by multiples of 64 and by odd amounts.  Full tables against the oracle, with
-    and without the shortcut, with and without records."""
+    """By default a group of 64 budgets whose candidates are constant is computed once.  Layer-0
+    memories are placed so that the columns change exactly at, just before and just after the
+    group boundaries (budgets 63, 64, 65, 127, 128, ...), at budget 0, at E and beyond E, in
+    launches of 4968 and 4140 groups whose last one is cut by E; later layers shift by multiples
+    of 64 and by odd amounts.  Full tables against the oracle, pruned and dense, with and without
+    records."""
     E = 26453                                       # E + 1 = 103 * 256 + 86: a ragged last wave
     flags = MODES[mode]
     edges = [0, 1, 63, 64, 65, 127, 128, 129, 191, 192, 4095, 4096, 4097, E - 64, E - 63, E - 1, E, E + 1]
@@ -417,7 +416,7 @@ def test_runs_of_equal_columns_edge_cases(g, S, mode):
         parts.append(gi.Problem(1, S, E, np.array([L]), c, M, R))
     p = gi.stack(parts, f"runs-S{S}")
     keep = 0 if flags & 16 else g.GBMW_FLAG_KEEP_ALL_C
-    # one stream: every layer's launch then covers all instances (1248 and 1040 workgroups)
+    # one stream: every layer's launch then covers all instances
     ctx = solve_gpu(p, flags=flags | keep | g.GBMW_FLAG_ONE_STREAM, device_inputs=True)
     best, best_s = g.gbmw_get_best(ctx)
     for b in range(p.B):
@@ -429,10 +428,11 @@ def test_runs_of_equal_columns_edge_cases(g, S, mode):
 @pytest.mark.parametrize("mode", list(MODES), ids=list(MODES))
 @pytest.mark.parametrize("E", [0, 5, 100, 300, 767])
 def test_many_small_instances_in_one_launch(g, E, mode):
-    """Hundreds of instances with one to three workgroups each: a launch large enough for the
-    unsplit shape whose workgroups are mostly cut by the end of the table (waves entirely
-    beyond E, a ragged last wave, E + 1 a multiple of 256 for E = 767).  Integer costs, so runs
-    of equal columns and ties are everywhere.  Every 37th instance cell by cell, best rows of all."""
+    """Hundreds of instances of one to three workgroups each, mostly cut by the end of the table (waves
+    entirely beyond E, a ragged last wave, E + 1 a multiple of 256 for E = 767): by default the pruned
+    step for E = 300 and 767 and the dense kernel's unsplit shape below (the pruned step there:
+    test_pruned_step_over_one_and_two_groups).  Integer costs, so runs of equal columns and ties are
+    everywhere.  Every 37th instance cell by cell, best rows of all."""
     flags = MODES[mode]
     B, S = 700, 7
     st = gi.Stream(8800 + E)
@@ -459,13 +459,13 @@ def test_many_small_instances_in_one_launch(g, E, mode):
 @pytest.mark.parametrize("mode", list(MODES), ids=list(MODES))
 @pytest.mark.parametrize("streams", ["one-stream", "two-groups"])
 def test_launch_shapes_follow_one_another(g, mode, streams):
-    """Six instances of 2..7 layers over 120 row tiles: the layer launches shrink from the unsplit
-    shape (6 x 120 workgroups) to the split one, so that a split launch reads tables that an
-    unsplit launch with the run shortcut left (cells of uniform groups unwritten, the summary
-    words standing for them), later split launches read tables that split launches wrote, and
-    the final reduce, the export and the walkers read both kinds.  Two kinds of inputs: integer
-    costs with coarse memory (long runs, ties) and random ones (few runs).  Every cell of every
-    layer against the oracle."""
+    """Six instances of 2..7 layers over 480 groups of 64 budgets: the layer launches shrink.  On one
+    stream by default from a group per wave (2880 groups) to four waves per group, each shape
+    reading tables that the other left (cells of constant groups unwritten, the summary words
+    standing for them); there with dense arithmetic from the unsplit to the split kernel; in two
+    groups of instances the split dense kernel throughout.  The final reduce, the export and the
+    walkers read what they left.  Two kinds of inputs: integer costs with coarse memory (long runs, ties) and random ones
+    (few runs).  Every cell of every layer against the oracle."""
     flags = MODES[mode] | (g.GBMW_FLAG_ONE_STREAM if streams == "one-stream" else 0)
     S, E = 9, 120 * 256 - 77
     for kind in (0, 1):
@@ -548,7 +548,7 @@ def test_config5_large_batched_full_size(g):
 
 
 def test_config5_all_modes_agree(g):
-    """cfg5 under the four combinations of records / values only and run shortcut / dense
+    """cfg5 under the four combinations of records / values only and pruned step / dense
     arithmetic: best rows, their argmins, the last layer's table and the records of two
     layers of one instance are the same bytes (the default mode is checked against the
     oracle above)."""

@@ -35,7 +35,7 @@ def test_minplus_instantiations_do_not_spill(blocks):
         assert scratch == 0, f"{name}: {scratch} bytes of scratch per lane"
         assert occ >= int(m.group(2)), f"{name}: occupancy {occ} below the requested {m.group(2)}"
     assert seen == 288         # S' = 4..64 in steps of 4; first-layer and later-layer; with and without argmin records;
-                               # three launch shapes (split, and unsplit with and without the run shortcut), and the
+                               # three launch shapes (split, unsplit and the pruned step), and the
                                # counting twin of the last (measurements only, no occupancy target); S' = 68..128: with and
                                # without records
 
